@@ -168,9 +168,32 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Wait for this wave's vector memory operations (the direct global -> LDS loads).
-__device__ __forceinline__ void wait_vm0() {
-  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt 0; expcnt and lgkmcnt not waited for
+typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
+typedef float f32v2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  const bf16v2 v = __builtin_convertvector(f32v2{lo, hi}, bf16v2);  // round to nearest even
+  uint32_t u;
+  __builtin_memcpy(&u, &v, 4);
+  return u;
+}
+
+// Wait until at most N of this wave's vector memory operations (the direct
+// global -> LDS loads) are in flight; expcnt and lgkmcnt are not waited for.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// Barrier between the parts of a phase: nothing moves across it, and nothing
+// is waited for (the waits that matter stand before it or come with the uses).
+__device__ __forceinline__ void phase_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
 }
 
 // A row of 8 16-byte chunks stored at chunk position c ^ ((r >> 1) & 7): the 16
@@ -178,10 +201,11 @@ __device__ __forceinline__ void wait_vm0() {
 __device__ __forceinline__ int swz8(int r, int c) { return r * 8 + (c ^ ((r >> 1) & 7)); }
 
 // ---------------------------------------------------------------------------
-// Linear: Y = X W^T (+ R).  One 256-thread workgroup per 128 x 128 tile of Y,
-// 2 x 2 waves of 64 x 64 (4 x 4 accumulator blocks); K staged 64 at a time
-// through two LDS buffers with the global loads of the stage after next held
-// in registers (zero-filled past K).  Needs 16-byte aligned rows and K % 8 == 0.
+// Linear: Y = X W^T (+ R), K % 64 != 0, short K and widths that fill larger tiles
+// badly.  One 256-thread workgroup per 128 x 128 tile of Y, 2 x 2 waves of 64 x 64
+// (4 x 4 accumulator blocks); K staged 64 at a time through two LDS buffers with
+// the global loads of the stage after next held in registers (zero-filled past
+// K).  Needs 16-byte aligned rows and K % 8 == 0.
 // ---------------------------------------------------------------------------
 constexpr int kLinT = 128, kLinK = 64;
 
@@ -277,6 +301,226 @@ __global__ __launch_bounds__(256, 2) void lin_kernel(const uint16_t* __restrict_
       }
 }
 
+// ---------------------------------------------------------------------------
+// Linear, K % 64 == 0: a tile of 256 n by TM m (256, or 128 for launches that
+// would leave CUs idle) of Y per 512-thread workgroup (one per CU), eight waves of
+// v_mfma_f32_16x16x32_bf16 accumulators: 2 x 4 waves of 128 (n) x 64 (m), or
+// 4 x 2 of 64 x 64.  The tile is computed as (W X^T)'s, so that a lane holds four
+// consecutive n of one token.  K goes in stages of 64 (whole 128-byte lines of
+// both operands), two stages in LDS.  The rows a wave reads are split in two
+// halves, W0 / W1 and X0 / X1; a unit of LDS is one half of one operand for all
+// waves.  A stage is four phases, W0 X0, W0 X1, W1 X1, W1 X0, of 16 (8) MFMAs, and
+// each phase has a memory part (the fragment reads of its MFMAs, and the direct
+// global -> LDS load of one unit that died two phases ago, for the stage after
+// next) and a matrix part, with a barrier after each.  Waves 4-7 run one barrier
+// behind waves 0-3: on every SIMD one wave is in its matrix part while the other
+// is in its memory part.  A unit is loaded six phases before it is read.
+// Bound: MFMA issue and the clock under that load.  Measured (16384 x 4096 ->
+// 11008): 1847 us (800 TFLOP/s) on 128 tiles with the operands staged through
+// registers, 1011 us (1462 TFLOP/s) here; the same tile with all eight waves in
+// step and a ring of five slots 1190 us; one stage per trip of the loop (with
+// copies of the X0 fragments) 1082 us.
+// ---------------------------------------------------------------------------
+constexpr int kLinB = 256;
+
+template <int TM>
+struct LinGeo {
+  static constexpr int NWM = TM / 64, NWN = 8 / NWM;  // waves along m and n
+  static constexpr int HW = kLinB / NWN / 2;          // rows per wave and W half
+  static constexpr int HA = HW / 16;                  // their 16-row blocks (X half: 32 rows, 2 blocks)
+  static constexpr int UW = 128 * 128;                // bytes of a W unit (128 rows)
+  static constexpr int UX = 32 * NWM * 128;           // of an X unit
+  static constexpr int LW = 2, LX = UX / 8192;        // wave-wide loads per wave and unit
+  static constexpr int PAR = 2 * (UW + UX);           // one stage
+  static constexpr int ELS = kLinB * 4 + 16;          // epilogue: fp32 row stride in bytes, 128 rows per pass
+  static constexpr size_t LDS = (size_t)128 * ELS > (size_t)2 * PAR ? (size_t)128 * ELS : (size_t)2 * PAR;
+};
+
+template <int TM>
+__global__ __launch_bounds__(512) void lin256_kernel(const uint16_t* __restrict__ X, int64_t ldx,
+                                                     const uint16_t* __restrict__ W, int64_t ldw, const uint16_t* R,
+                                                     int64_t ldr, uint16_t* Y, int64_t ldy, int M, int N, int K,
+                                                     int vec) {
+  using G = LinGeo<TM>;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lsm[];  // [stage parity][W0, W1, X0, X1]
+  constexpr int GB = 4, HA = G::HA;
+  const int tm = (M + TM - 1) / TM, tn = (N + kLinB - 1) / kLinB;
+  const int per = (int)((gridDim.x + 7) / 8);
+  const int id = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);  // contiguous tile ranges per XCD
+  if (id >= tm * tn) return;
+  // bands of 4 row tiles walked across the columns: the 32 workgroups of an
+  // XCD hold 4 x 8 tiles, whose operand panels they share in its L2
+  const int b0 = id / (GB * tn) * GB, bh = min(GB, tm - b0), br = id - b0 * tn;
+  const int i0 = (b0 + br % bh) * TM, j0 = (br / bh) * kLinB;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = wave / G::NWM, wj = wave % G::NWM;  // place along n, m
+  const int g = lane >> 4, l16 = lane & 15;
+
+  // this lane's chunk of each of the wave's loads per unit (8 unit rows of 128
+  // bytes each); unit row u of W half h is tile row 2 HW (u / HW) + HW h + u % HW,
+  // of X half h 64 (u / 32) + 32 h + u % 32
+  const uint16_t* src[4][2];  // [W0, W1, X0, X1]
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int uw = wave * 16 + 8 * j + (lane >> 3), ux = wave * 8 * G::LX + 8 * j + (lane >> 3);
+    const int cw = (lane & 7) ^ ((uw >> 1) & 7), cx = (lane & 7) ^ ((ux >> 1) & 7);
+    const int rw = 2 * G::HW * (uw / G::HW) + uw % G::HW, rx = 64 * (ux >> 5) + (ux & 31);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      src[h][j] = W + (int64_t)min(j0 + rw + G::HW * h, N - 1) * ldw + 8 * cw;
+      src[2 + h][j] = X + (int64_t)min(i0 + rx + 32 * h, M - 1) * ldx + 8 * cx;
+    }
+  }
+  const int nst = K / 64;
+  // unit `op` of stage st (of parity par; past the last stage: the last one again,
+  // into a slot that is read no more)
+  auto issue = [&](int op, int st, int par) {
+    const int nl = op < 2 ? G::LW : G::LX;
+    uint8_t* dst = lsm + par * G::PAR + (op < 2 ? op * G::UW : 2 * G::UW + (op - 2) * G::UX) + wave * nl * 1024;
+    const int64_t off = (int64_t)min(st, nst - 1) * 64;
+#pragma unroll
+    for (int j = 0; j < nl; ++j)
+      __builtin_amdgcn_global_load_lds((const void*)(src[op][j] + off),
+                                       (__attribute__((address_space(3))) void*)(dst + j * 1024), 16, 0, 0);
+  };
+  f4 acc[2 * HA][4];
+#pragma unroll
+  for (int a = 0; a < 2 * HA; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+
+  // fragment offsets within a unit; k-step 1 of a stage is chunk ^ 4
+  const uint32_t fw = (uint32_t)((wi * G::HW + l16) * 128 + ((g ^ (l16 >> 1)) * 16));
+  const uint32_t fx = (uint32_t)((wj * 32 + l16) * 128 + ((g ^ (l16 >> 1)) * 16));
+  auto read_w = [&](int par, int h, u32x4 (&F)[2][HA]) {
+    const uint8_t* p = lsm + par * G::PAR + h * G::UW;
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+      for (int a = 0; a < HA; ++a) F[s2][a] = *(const u32x4*)(p + (fw ^ (64u * s2)) + a * 2048);
+  };
+  auto read_x = [&](int par, int h, u32x4 (&F)[2][2]) {
+    const uint8_t* p = lsm + par * G::PAR + 2 * G::UW + h * G::UX;
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) F[s2][b] = *(const u32x4*)(p + (fx ^ (64u * s2)) + b * 2048);
+  };
+  // End of a memory part: the unit that the next phase reads has landed.  It was
+  // issued six phases before that one; five units came after it, W and X ones
+  // in turn (the last of them a W one in phases 0 and 2).
+  auto mem_end = [&](int phase) {
+    if (phase & 1)
+      wait_vm<3 * G::LX + 2 * G::LW>();
+    else
+      wait_vm<3 * G::LW + 2 * G::LX>();
+    phase_barrier();
+  };
+  auto mma = [&](int hw, int hx, const u32x4 (&Fw)[2][HA], const u32x4 (&Fx)[2][2]) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+      for (int a = 0; a < HA; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[HA * hw + a][2 * hx + b] = mma_bf16(Fw[s2][a], Fx[s2][b], acc[HA * hw + a][2 * hx + b]);
+    __builtin_amdgcn_s_setprio(0);
+    phase_barrier();
+  };
+
+  issue(2, 0, 0);
+  issue(0, 0, 0);
+  issue(3, 0, 0);
+  issue(1, 0, 0);
+  issue(2, 1, 1);
+  issue(0, 1, 1);
+  issue(3, 1, 1);
+  u32x4 w[2][HA], x1[2][2], xa[2][2], xb[2][2];
+  mem_end(3);  // X0 and W0 of stage 0
+  read_x(0, 0, xa);
+  if (wave >> 2) phase_barrier();  // these four waves run one barrier behind
+  // x0: X0 of stage t, nx: takes X0 of stage t + 1
+  auto stage = [&](int t, int par, const u32x4 (&x0)[2][2], u32x4 (&nx)[2][2]) {
+    read_w(par, 0, w);
+    issue(1, t + 1, par ^ 1);
+    mem_end(0);
+    mma(0, 0, w, x0);
+    read_x(par, 1, x1);
+    issue(2, t + 2, par);
+    mem_end(1);
+    mma(0, 1, w, x1);
+    read_w(par, 1, w);
+    issue(0, t + 2, par);
+    mem_end(2);
+    mma(1, 1, w, x1);
+    read_x(par ^ 1, 0, nx);
+    issue(3, t + 2, par);
+    mem_end(3);
+    mma(1, 0, w, x0);
+  };
+  int t = 0;
+  for (; t + 1 < nst; t += 2) {  // two stages per trip: static slots, and no copies of X0
+    stage(t, 0, xa, xb);
+    stage(t + 1, 1, xb, xa);
+  }
+  if (t < nst) stage(t, 0, xa, xb);
+  if (!(wave >> 2)) phase_barrier();
+#pragma unroll
+  for (int a = 0; a < 2 * HA; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) asm volatile("s_nop 1" : "+v"(acc[a][b]));  // the last products have been written
+  wait_vm<0>();  // the loads past the last stage: the epilogue reuses the LDS
+
+  // accumulator element r of block (a, b): n = 2 HW wi + 16 a + 4 g + r, m = 64 wj + 16 b + l16
+  if (vec) {
+    // residual added in fp32, one rounding; staged through LDS, 128 tokens per
+    // pass, so that global accesses are 16 bytes per lane
+#pragma unroll
+    for (int h = 0; h < TM / 128; ++h) {
+      lds_barrier();
+      if (wj >> 1 == h)
+#pragma unroll
+        for (int a = 0; a < 2 * HA; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            *(f4*)(lsm + ((wj & 1) * 64 + b * 16 + l16) * G::ELS + (wi * 2 * G::HW + a * 16 + 4 * g) * 4) = acc[a][b];
+      lds_barrier();
+#pragma unroll 4
+      for (int q = tid; q < 128 * (kLinB / 8); q += 512) {
+        const int rr = q / (kLinB / 8), c8 = (q % (kLinB / 8)) * 8;
+        const int i = i0 + h * 128 + rr, j = j0 + c8;
+        if (i >= M || j >= N) continue;
+        const f4 v0 = *(const f4*)(lsm + rr * G::ELS + c8 * 4), v1 = *(const f4*)(lsm + rr * G::ELS + c8 * 4 + 16);
+        float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+        if (R) {
+          const u32x4 rv = *(const u32x4*)(R + (int64_t)i * ldr + j);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] += bf16_bits_to_f32((uint16_t)(rv[e >> 1] >> (16 * (e & 1))));
+        }
+        u32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
+        *(u32x4*)(Y + (int64_t)i * ldy + j) = o;
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int a = 0; a < 2 * HA; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = i0 + wj * 64 + b * 16 + l16, j = j0 + wi * 2 * G::HW + a * 16 + 4 * g + r;
+        if (i < M && j < N) {
+          float v = acc[a][b][r];
+          if (R) v += bf16_bits_to_f32(R[(int64_t)i * ldr + j]);
+          Y[(int64_t)i * ldy + j] = f32_to_bf16_bits(v);
+        }
+      }
+}
+
 // Linear for rows that are not 16-byte aligned or K % 8 != 0: one thread per
 // output, fp32 sum in k order.
 __global__ void lin_plain_kernel(const uint16_t* __restrict__ X, int64_t ldx, const uint16_t* __restrict__ W,
@@ -319,8 +563,6 @@ __global__ void lin_plain_kernel(const uint16_t* __restrict__ X, int64_t ldx, co
 // The query blocks of one (sequence, head) run on one XCD and share its K and
 // V in that XCD's L2.
 // ---------------------------------------------------------------------------
-typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
-typedef float f32v2 __attribute__((ext_vector_type(2)));
 typedef short s16v4 __attribute__((ext_vector_type(4)));
 typedef float f16x __attribute__((ext_vector_type(16)));
 
@@ -329,13 +571,6 @@ __device__ __forceinline__ f16x mma32_bf16(const u32x4& a, const u32x4& b, f16x 
   __builtin_memcpy(&av, &a, 16);
   __builtin_memcpy(&bv, &b, 16);
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const bf16v2 v = __builtin_convertvector(f32v2{lo, hi}, bf16v2);  // round to nearest even
-  uint32_t u;
-  __builtin_memcpy(&u, &v, 4);
-  return u;
 }
 
 template <int HD, int NW>
@@ -413,7 +648,7 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* _
   int kb = 0;
   do {  // two key blocks per trip; nkb >= 1
     const int buf = (kb >> 1) & 1;
-    wait_vm0();     // this wave's part of the blocks landed
+    wait_vm<0>();     // this wave's part of the blocks landed
     lds_barrier();  // every wave's; and every wave is done with the blocks before
     if (kb + 2 < nkb) {
       issue(Kx, kb + 2, sm[buf ^ 1][0], false);
@@ -469,7 +704,7 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* _
   issue(V, 0, sm[0][1], true);
   kb = 0;
   do {
-    wait_vm0();
+    wait_vm<0>();
     lds_barrier();
     if (kb + 1 < nkb) {
       issue(Kx, kb + 1, sm[(kb + 1) & 1][0], false);
@@ -598,6 +833,29 @@ duo_status duo_linear(const void* X, int64_t m, int64_t k, int64_t ldx, const vo
   const bool vec = k % 8 == 0 && ldx % 8 == 0 && ldw % 8 == 0 && aligned16(X) && aligned16(W);
   if (vec) {
     const int64_t tiles = cdiv(m, kLinT) * cdiv(n, kLinT);
+    // Microseconds of the three tile sizes: rounds of the chip (256 CUs with one
+    // tile each; two of the 128 tiles) times a fixed part (launch, first loads,
+    // epilogue) and a part per k, fitted to measured launches (m x k -> n: 4096 x
+    // 4096 -> 4096 95, 57.5 x 2 and 181 us; 40000 x 512 -> 300 41, 46 and 38 us).
+    // The 128 tile keeps short sums and widths that fill 256 badly.
+    const int64_t t256 = cdiv(m, 256) * cdiv(n, kLinB), t128 = cdiv(m, 128) * cdiv(n, kLinB);
+    const double c256 = (double)cdiv(t256, 256) * (9.5 + 0.0213 * (double)k);
+    const double c128 = (double)cdiv(t128, 256) * (7.5 + 0.0122 * (double)k);
+    const double cold = (double)cdiv(tiles, 512) * (7.8 + 0.0201 * (double)k);
+    if (k % 64 == 0 && (c256 <= cold || c128 <= cold)) {
+      const int vy = n % 8 == 0 && ldy % 8 == 0 && aligned16(Y) && (!R || (ldr % 8 == 0 && aligned16(R)));
+      auto go = [&](auto kern, int64_t nt, size_t lds) -> duo_status {
+        if (nt > INT32_MAX) return DUO_ERR_UNSUPPORTED;
+        if (duo_status st = set_max_lds((const void*)kern, lds); st != DUO_OK) return st;
+        hipLaunchKernelGGL(kern, dim3((unsigned)rup(nt, 8)), dim3(512), lds, s, (const uint16_t*)X, ldx,
+                           (const uint16_t*)W, ldw, (const uint16_t*)R, ldr, (uint16_t*)Y, ldy, (int)m, (int)n, (int)k,
+                           vy);
+        DUO_LAUNCH_CHECK();
+        return DUO_OK;
+      };
+      if (c256 <= c128) return go(lin256_kernel<256>, t256, LinGeo<256>::LDS);
+      return go(lin256_kernel<128>, t128, LinGeo<128>::LDS);
+    }
     if (tiles > INT32_MAX) return DUO_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(lin_kernel, dim3((unsigned)rup(tiles, 8)), dim3(256), 0, s, (const uint16_t*)X, ldx,
                        (const uint16_t*)W, ldw, (const uint16_t*)R, ldr, (uint16_t*)Y, ldy, (int)m, (int)n, (int)k);
