@@ -19,8 +19,10 @@
 #include <mutex>
 
 #include "internal.h"
+#include "pingpong.h"
 
 using namespace duo;
+using namespace duo::pp;
 
 namespace {
 
@@ -146,28 +148,6 @@ __global__ void silu_mul_kernel(const uint16_t* __restrict__ G, const uint16_t* 
   Y[t * ldy + c] = f32_to_bf16_bits(g / (1.0f + expf(-g)) * u);
 }
 
-// ---------------------------------------------------------------------------
-// bf16 MFMA building blocks (v_mfma_f32_16x16x32_bf16: lane l holds row l % 16
-// of A and column l % 16 of B, each as the 8 consecutive k of group l / 16; the
-// accumulator's element r sits at row 4 (l / 16) + r, column l % 16)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ f4 mma_bf16(const u32x4& a, const u32x4& b, f4 c) {
-  bf16x8 av, bv;
-  __builtin_memcpy(&av, &a, 16);
-  __builtin_memcpy(&bv, &b, 16);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
-}
-
-// Workgroup barrier without the memory fence of __syncthreads, whose fence
-// would wait for the global prefetches in flight; this wave's LDS traffic is
-// drained first.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
 typedef float f32v2 __attribute__((ext_vector_type(2)));
 
@@ -176,24 +156,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   uint32_t u;
   __builtin_memcpy(&u, &v, 4);
   return u;
-}
-
-// Wait until at most N of this wave's vector memory operations (the direct
-// global -> LDS loads) are in flight; expcnt and lgkmcnt are not waited for.
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-// Barrier between the parts of a phase: nothing moves across it, and nothing
-// is waited for (the waits that matter stand before it or come with the uses).
-__device__ __forceinline__ void phase_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
 }
 
 // A row of 8 16-byte chunks stored at chunk position c ^ ((r >> 1) & 7): the 16
@@ -305,21 +267,13 @@ __global__ __launch_bounds__(256, 2) void lin_kernel(const uint16_t* __restrict_
 // Linear, K % 64 == 0: a tile of 256 n by TM m (256, or 128 for launches that
 // would leave CUs idle) of Y per 512-thread workgroup (one per CU), eight waves of
 // v_mfma_f32_16x16x32_bf16 accumulators: 2 x 4 waves of 128 (n) x 64 (m), or
-// 4 x 2 of 64 x 64.  The tile is computed as (W X^T)'s, so that a lane holds four
-// consecutive n of one token.  K goes in stages of 64 (whole 128-byte lines of
-// both operands), two stages in LDS.  The rows a wave reads are split in two
-// halves, W0 / W1 and X0 / X1; a unit of LDS is one half of one operand for all
-// waves.  A stage is four phases, W0 X0, W0 X1, W1 X1, W1 X0, of 16 (8) MFMAs, and
-// each phase has a memory part (the fragment reads of its MFMAs, and the direct
-// global -> LDS load of one unit that died two phases ago, for the stage after
-// next) and a matrix part, with a barrier after each.  Waves 4-7 run one barrier
-// behind waves 0-3: on every SIMD one wave is in its matrix part while the other
-// is in its memory part.  A unit is loaded six phases before it is read.
-// Bound: MFMA issue and the clock under that load.  Measured (16384 x 4096 ->
-// 11008): 1847 us (800 TFLOP/s) on 128 tiles with the operands staged through
-// registers, 1011 us (1462 TFLOP/s) here; the same tile with all eight waves in
-// step and a ring of five slots 1190 us; one stage per trip of the loop (with
-// copies of the X0 fragments) 1082 us.
+// 4 x 2 of 64 x 64, in the loop of pingpong.h.  The tile is computed as (W X^T)'s,
+// so that a lane holds four consecutive n of one token; a stage is 64 k (whole
+// 128-byte lines of both operands).  Bound: MFMA issue and the clock under that
+// load.  Measured (16384 x 4096 -> 11008): 1847 us (800 TFLOP/s) on 128 tiles with
+// the operands staged through registers, 1011 us (1462 TFLOP/s) here; the same
+// tile with all eight waves in step and a ring of five slots 1190 us; one stage
+// per trip of the loop (with copies of the B0 fragments) 1082 us.
 // ---------------------------------------------------------------------------
 constexpr int kLinB = 256;
 
@@ -406,71 +360,7 @@ __global__ __launch_bounds__(512) void lin256_kernel(const uint16_t* __restrict_
 #pragma unroll
       for (int b = 0; b < 2; ++b) F[s2][b] = *(const u32x4*)(p + (fx ^ (64u * s2)) + b * 2048);
   };
-  // End of a memory part: the unit that the next phase reads has landed.  It was
-  // issued six phases before that one; five units came after it, W and X ones
-  // in turn (the last of them a W one in phases 0 and 2).
-  auto mem_end = [&](int phase) {
-    if (phase & 1)
-      wait_vm<3 * G::LX + 2 * G::LW>();
-    else
-      wait_vm<3 * G::LW + 2 * G::LX>();
-    phase_barrier();
-  };
-  auto mma = [&](int hw, int hx, const u32x4 (&Fw)[2][HA], const u32x4 (&Fx)[2][2]) {
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int a = 0; a < HA; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[HA * hw + a][2 * hx + b] = mma_bf16(Fw[s2][a], Fx[s2][b], acc[HA * hw + a][2 * hx + b]);
-    __builtin_amdgcn_s_setprio(0);
-    phase_barrier();
-  };
-
-  issue(2, 0, 0);
-  issue(0, 0, 0);
-  issue(3, 0, 0);
-  issue(1, 0, 0);
-  issue(2, 1, 1);
-  issue(0, 1, 1);
-  issue(3, 1, 1);
-  u32x4 w[2][HA], x1[2][2], xa[2][2], xb[2][2];
-  mem_end(3);  // X0 and W0 of stage 0
-  read_x(0, 0, xa);
-  if (wave >> 2) phase_barrier();  // these four waves run one barrier behind
-  // x0: X0 of stage t, nx: takes X0 of stage t + 1
-  auto stage = [&](int t, int par, const u32x4 (&x0)[2][2], u32x4 (&nx)[2][2]) {
-    read_w(par, 0, w);
-    issue(1, t + 1, par ^ 1);
-    mem_end(0);
-    mma(0, 0, w, x0);
-    read_x(par, 1, x1);
-    issue(2, t + 2, par);
-    mem_end(1);
-    mma(0, 1, w, x1);
-    read_w(par, 1, w);
-    issue(0, t + 2, par);
-    mem_end(2);
-    mma(1, 1, w, x1);
-    read_x(par ^ 1, 0, nx);
-    issue(3, t + 2, par);
-    mem_end(3);
-    mma(1, 0, w, x0);
-  };
-  int t = 0;
-  for (; t + 1 < nst; t += 2) {  // two stages per trip: static slots, and no copies of X0
-    stage(t, 0, xa, xb);
-    stage(t + 1, 1, xb, xa);
-  }
-  if (t < nst) stage(t, 0, xa, xb);
-  if (!(wave >> 2)) phase_barrier();
-#pragma unroll
-  for (int a = 0; a < 2 * HA; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) asm volatile("s_nop 1" : "+v"(acc[a][b]));  // the last products have been written
-  wait_vm<0>();  // the loads past the last stage: the epilogue reuses the LDS
+  pp_loop<HA, G::LW, G::LX>(nst, acc, issue, read_w, read_x);
 
   // accumulator element r of block (a, b): n = 2 HW wi + 16 a + 4 g + r, m = 64 wj + 16 b + l16
   if (vec) {

@@ -18,6 +18,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "pingpong.h"
 
 namespace duo {
 
@@ -545,7 +546,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* __restrict__ Xs, con
 
   for (int tt = 0; tt < 8; ++tt) {
     const int tok0 = tsb + tt * kTokBlk;
-    if (tok0 >= mc) break;  // uniform
+    if (tok0 >= (int)rup(mc, 2 * kTokBlk)) break;  // uniform; zeros fill up the last pair of token blocks
     const int t = tok0 + tr;
     const bool tok_ok = t < mc;
     const int64_t th = tok_ok ? thr[t] : INT64_MAX;
@@ -627,7 +628,7 @@ __global__ __launch_bounds__(256) void pack16_kernel(const uint16_t* __restrict_
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
   for (int tt = 0; tt < 8; ++tt) {
     const int tb = blockIdx.y * 8 + tt;
-    if (tb * kTokBlk >= mc) break;  // uniform
+    if (tb * kTokBlk >= (int)rup(mc, 2 * kTokBlk)) break;  // uniform; zeros fill up the last pair of token blocks
     const int tbase = tb * kTokBlk + 8 * wave;
     u32x4 xs[8], xd[8];
     int64_t th[8];
@@ -750,16 +751,19 @@ template <typename T>
 struct GramArgs {
   const T* Ph;  // packed Xh
   const T* Pz;  // packed dX (single stream) or its high part (two streams)
-  const T* Pl;  // packed low part of dX (two bf16 streams), else unused
+  const T* Pl;  // packed low part of dX (two bf16 streams), else NULL
   int kp, k, nt;     // padded channels, channels, kp / 256
   int nh, ntiles;    // H tiles (0 when H is not wanted) and H + G tiles
   int g_full;        // G tiles: all nt x nt (1) or the upper triangle I <= J (0)
-  int nseg, seg_len, ntb;
+  int mixed;         // two bf16 streams: G tiles cost twice an H tile and come first
+  int nsplit, nseg;  // the last nsplit tiles of the order are split into nseg token segments
+  int seg_len, ntb;  // token blocks per segment, in all
+  int piece;         // token blocks that one set of accumulators sums up
   float* H;
   int64_t ldh;
   float* G;
   int64_t ldg;
-  float* part;  // [nseg][ntiles][256 * 256] when nseg > 1
+  float* part;  // [nseg][nsplit][256 * 256]
   int vec4;     // k, ldh, ldg multiples of 4 and H, G 16-byte aligned: 16-byte reduction path
 };
 
@@ -813,99 +817,142 @@ __device__ inline void gram_tile(int t, int nh, int nt, int g_full, int* isg, in
   *I = b0 + r % h;
 }
 
-__device__ inline int xcd_remap(int b, int nblocks) {
-  const int per = (nblocks + 7) / 8;
-  return (b % 8) * per + b / 8;
-}
-
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
+// fp32: two fragments per stage, four 16x16x4 fp32 MFMAs each; in fragment f, lane
+// group l/16 holds the 4 tokens of group 4f + l/16 (the same tokens on both
+// operands, so the sum runs over all 32 tokens of the stage)
+__device__ inline f4 mma_f32(const v4u& a, const v4u& b, f4 c) {
+  const float* x = (const float*)&a;
+  const float* y = (const float*)&b;
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], y[0], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], y[1], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], y[2], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], y[3], c, 0, 0, 0);
+  return c;
+}
+
+// Tile number o of the launch order: H then G, or (mixed) G then H.
 template <typename T>
-struct MfmaOp;
-template <>
-struct MfmaOp<uint16_t> {
-  // one 16x16x32 bf16 MFMA per fragment pair per 32-token stage
-  static constexpr int kFrags = 1;
-  __device__ static inline f4 mma(const v4u& a, const v4u& b, f4 c) {
-    bf16x8 av, bv;
-    __builtin_memcpy(&av, &a, 16);
-    __builtin_memcpy(&bv, &b, 16);
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
-  }
-};
-template <>
-struct MfmaOp<float> {
-  // two fragments per stage, four 16x16x4 fp32 MFMAs each; in fragment f, lane
-  // group l/16 holds the 4 tokens of group 4f + l/16 (the same tokens on both
-  // operands, so the sum runs over all 32 tokens of the stage)
-  static constexpr int kFrags = 2;
-  __device__ static inline f4 mma(const v4u& a, const v4u& b, f4 c) {
-    const float* x = (const float*)&a;
-    const float* y = (const float*)&b;
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], y[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], y[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], y[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], y[3], c, 0, 0, 0);
-    return c;
-  }
-};
-
-// Wait until at most N of this wave's vector-memory operations (here: the
-// direct global->LDS loads) are still in flight.
-template <int N>
-__device__ __forceinline__ void wait_vmem() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70 | 0xF00);
+__device__ inline int gram_order(const GramArgs<T>& A, int o) {
+  const int ng = A.ntiles - A.nh;
+  return !A.mixed ? o : (o < ng ? A.nh + o : o - ng);
 }
 
-// Workgroup barrier without the memory fence of __syncthreads (whose fence
-// would also wait for every prefetch in flight).  LDS traffic of this wave is
-// drained first; the empty asm statements keep the compiler from moving memory
-// accesses across the barrier.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+// Work of a workgroup: a whole tile (*part < 0), or token segment *seg of a split
+// tile whose partial is number *part.  Each XCD takes a contiguous range of the
+// whole tiles (of the whole G tiles and of the whole H tiles when mixed: an XCD
+// that held only the dearer kind would finish last; neighbouring tiles share
+// operand panels in that XCD's L2), then one of the segments, segment by segment.
+template <typename T>
+__device__ inline bool gram_unit(const GramArgs<T>& A, int* tile, int* seg, int* part) {
+  const int x = blockIdx.x % 8;
+  int y = blockIdx.x / 8;
+  const int nfull = A.ntiles - A.nsplit;
+  const int n1 = A.mixed ? min(A.ntiles - A.nh, nfull) : nfull, n2 = nfull - n1, n3 = A.nsplit * A.nseg;
+  const int p1 = (n1 + 7) / 8, p2 = (n2 + 7) / 8, p3 = (n3 + 7) / 8;
+  *seg = 0;
+  *part = -1;
+  if (y < p1) {
+    *tile = gram_order(A, x * p1 + y);
+    return x * p1 + y < n1;
+  }
+  y -= p1;
+  if (y < p2) {
+    *tile = gram_order(A, n1 + x * p2 + y);
+    return x * p2 + y < n2;
+  }
+  y -= p2;
+  const int v = x * p3 + y;
+  if (y >= p3 || v >= n3) return false;
+  *seg = v / A.nsplit;
+  *part = v;
+  *tile = gram_order(A, nfull + v % A.nsplit);
+  return true;
 }
 
-// 512 threads = 8 waves in a 2 x 4 grid; each wave owns 128 rows x 64 columns
-// of the tile (8 x 4 accumulator blocks of 16 x 16).  Operand tiles stream
-// through a ring of NS LDS stages (one 32-token block each) filled by direct
-// global->LDS loads (global_load_lds_dwordx4: each lane moves 16 bytes, a wave
-// 1 KB), issued NS - 1 stages ahead (NS = 5 stages of 32 KB, or 3 of 48 KB
-// for the two-stream form, fill the 160 KB of LDS).  LDS layout of one operand tile:
-// [group][256 rows][16 bytes], identical to the packed global layout.
-template <typename T, bool HAS_LO, bool SHALLOW>
-__global__ __launch_bounds__(512) void gram_kernel(GramArgs<T> A) {
-  constexpr int EPG = 16 / (int)sizeof(T);
-  constexpr int NG = kTokBlk / EPG;
-  constexpr int TILE_B = GT * kTokBlk * (int)sizeof(T);
-  constexpr int NOP = HAS_LO ? 3 : 2;  // operand slots: B, A (hi), A lo
-  constexpr int STAGE_B = NOP * TILE_B;
-  constexpr int CHUNKS = TILE_B / 16;           // 16-byte chunks per operand tile
-  constexpr int DPW = NOP * CHUNKS / 64 / 8;    // wave-wide loads per wave per stage
-  constexpr int NS = (160 * 1024) / STAGE_B < 5 ? (160 * 1024) / STAGE_B : 5;  // ring depth
-  static_assert(NS >= 2 && CHUNKS % 64 == 0 && (NOP * CHUNKS / 64) % 8 == 0, "load split");
-  // fragment reads pipelined half a stage ahead: bf16, one stream (the
-  // register budget of the extra fragments is not there for the two-stream form)
-  constexpr bool PIPE = MfmaOp<T>::kFrags == 1 && !HAS_LO && NS >= 4;
-  // stages the pipelined form issues ahead of the one being read: NS - 1, or
-  // NS - 2 (SHALLOW; measured faster when the tokens are split into segments,
-  // slower with one long segment per tile)
-  constexpr int AHEAD = PIPE ? (SHALLOW ? NS - 2 : NS - 1) : NS - 1;
-  static_assert(!SHALLOW || PIPE, "the shallow ring is a form of the pipelined loop");
+// End of a piece in both Gram kernels: the tile's accumulators to the partial
+// tile of its segment (stored first, then added to), or added to H or G.  The
+// products run with the tile's columns (J) as the MFMA's rows, so that a lane
+// holds four consecutive entries of one row: accumulator element r of block (a,
+// b) is row 64 wj + 16 b + lane % 16, column 128 wi + 16 a + 4 (lane / 16) + r.
+// Sixteen 16-byte reads per lane are in flight at a time, with no LDS and no
+// barrier (staged through LDS, a piece cost 44 us at k = 4096; here 25).
+template <typename T>
+__device__ inline void gram_store(const GramArgs<T>& A, int isg, int I, int J, int part, bool first,
+                                  const f4 (&acc)[8][4]) {
+  // opaque, so that the addresses of a piece's stores are not kept in registers
+  // through the main loop
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = tid >> 6;
+  const int r0 = (wave & 3) * 64 + (lane & 15), c0 = (wave >> 2) * 128 + 4 * (lane >> 4);
+  float* base;  // of the tile
+  int64_t ld;
+  int rows = GT, cols = GT;
+  if (part >= 0) {
+    base = A.part + (int64_t)part * GT * GT;
+    ld = GT;
+  } else {
+    ld = isg ? A.ldg : A.ldh;
+    base = (isg ? A.G : A.H) + (int64_t)I * GT * ld + (int64_t)J * GT;
+    rows = min(GT, A.k - I * GT);
+    cols = min(GT, A.k - J * GT);
+    first = false;
+  }
+  if (part >= 0 || A.vec4) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float4 c[2][8];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+          const int row = r0 + 32 * h + 16 * b, col = c0 + 16 * a;
+          c[b][a] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (!first && row < rows && col < cols) c[b][a] = *(const float4*)(base + row * ld + col);
+        }
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+          const int row = r0 + 32 * h + 16 * b, col = c0 + 16 * a;
+          const f4 v = acc[a][2 * h + b];
+          if (row < rows && col < cols)
+            *(float4*)(base + row * ld + col) =
+                make_float4(c[b][a].x + v[0], c[b][a].y + v[1], c[b][a].z + v[2], c[b][a].w + v[3]);
+        }
+    }
+    return;
+  }
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = r0 + 16 * b, col = c0 + 16 * a + r;
+        if (row < rows && col < cols) base[row * ld + col] += acc[a][b][r];
+      }
+}
+
+// fp32 inputs.  512 threads = 8 waves in a 2 x 4 grid; each wave owns 128 columns x
+// 64 rows of the tile (8 x 4 accumulator blocks of 16 x 16).  Operand tiles
+// stream through two LDS stages (one 32-token block each, 64 KB) filled by
+// direct global->LDS loads (each lane moves 16 bytes, a wave 1 KB), one stage
+// ahead.  LDS layout of one operand tile: [group][256 rows][16 bytes], identical
+// to the packed global layout.
+constexpr int kGram32Stage = 2 * GT * kTokBlk * 4;
+__global__ __launch_bounds__(512) void gram_f32_kernel(GramArgs<float> A) {
+  constexpr int NG = kTokBlk / 4;
+  constexpr int CHUNKS = GT * kTokBlk * 4 / 16;  // 16-byte chunks per operand tile
+  constexpr int DPW = 2 * CHUNKS / 64 / 8;       // wave-wide loads per wave per stage
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-
-  const int u = xcd_remap(blockIdx.x, gridDim.x);
-  if (u >= A.ntiles * A.nseg) return;
-  const int seg = u / A.ntiles;
-  const int tile = u % A.ntiles;
-  int isg, I, J;
+  int seg, part, tile, isg, I, J;
+  if (!gram_unit(A, &tile, &seg, &part)) return;
   gram_tile(tile, A.nh, A.nt, A.g_full, &isg, &I, &J);
   const int tb0 = seg * A.seg_len;
-  const int tb1 = min(A.ntb, tb0 + A.seg_len);
-
+  const int tb1 = part < 0 ? A.ntb : min(A.ntb, tb0 + A.seg_len);
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wi = wave >> 2, wj = wave & 3;
@@ -918,223 +965,137 @@ __global__ __launch_bounds__(512) void gram_kernel(GramArgs<T> A) {
   for (int j = 0; j < DPW; ++j) {
     const int c0 = (wave * DPW + j) * 64;  // first chunk of this wave-wide load
     const int op = c0 / CHUNKS, c = c0 % CHUNKS + lane;
-    const T* base = op == 0 ? A.Ph : (op == 1 ? (isg ? A.Pz : A.Ph) : A.Pl);
+    const float* base = op == 0 || !isg ? A.Ph : A.Pz;
     const int blk = op == 0 ? J : I;
     src[j] = (const uint8_t*)base + ((int64_t)(c / GT) * A.kp + (int64_t)blk * GT + c % GT) * 16;
     ldso[j] = (uint32_t)(op * CHUNKS + c0 % CHUNKS) * 16;
   }
   auto issue = [&](int t) {
-    uint8_t* stage = smem + ((t - tb0) % NS) * STAGE_B;
+    uint8_t* stage = smem + ((t - tb0) & 1) * kGram32Stage;
 #pragma unroll
     for (int j = 0; j < DPW; ++j)
       __builtin_amdgcn_global_load_lds((const void*)(src[j] + (int64_t)t * tbs),
                                        (__attribute__((address_space(3))) void*)(stage + ldso[j]), 16, 0, 0);
   };
-
-  f4 acc[8][4];
+  int p0 = tb0;
+  do {  // pieces; an empty segment stores its zeros
+    const int p1 = min(tb1, p0 + A.piece);
+    f4 acc[8][4];
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+    for (int a = 0; a < 8; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
-
-  for (int t = tb0; t < min(tb1, tb0 + AHEAD); ++t) issue(t);
-  if (tb1 <= tb0) {
-    // empty segment: the partial tile stays zero
-  } else if constexpr (PIPE) {
-    // Half-stage pipeline: the second half of stage t's A fragments is read
-    // during the MFMAs of the first half, and the B and first-half A fragments
-    // of stage t + 1 during those of the second half, so the LDS reads of all
-    // eight waves overlap the matrix work instead of following each barrier.
-    const int fo = (lane >> 4) * GT + (lane & 15);
-    auto slot = [&](int t) { return (const v4u*)(smem + ((t - tb0) % NS) * STAGE_B); };
-    auto read_b = [&](int t, v4u (&F)[4]) {
-      const v4u* l_ = slot(t);
+      for (int b = 0; b < 4; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+    if (p0 < p1) issue(p0);
+    for (int t = p0; t < p1; ++t) {
+      pp::wait_vm<0>();
+      pp::lds_barrier();  // every wave's part of stage t has landed; stage t-1 is free
+      if (t + 1 < p1) issue(t + 1);
+      const v4u* l_ = (const v4u*)(smem + ((t - tb0) & 1) * kGram32Stage);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) F[b] = l_[fo + wj * 64 + b * 16];
-    };
-    auto read_a = [&](int t, int h2, v4u (&F)[4]) {
-      const v4u* l_ = slot(t);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) F[a] = l_[CHUNKS + fo + wi * 128 + (4 * h2 + a) * 16];
-    };
-    auto mma_half = [&](int h2, const v4u (&Fa)[4], const v4u (&Fb)[4]) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[4 * h2 + a][b] = MfmaOp<T>::mma(Fa[a], Fb[b], acc[4 * h2 + a][b]);
-    };
-    // stage t + 1 complete and readable by every wave; stage t + AHEAD issued
-    // into the slot of stage t + AHEAD - NS (t - 1 or t - 2), which every wave
-    // has finished reading
-    auto advance = [&](int t) {
-      switch (min(AHEAD - 2, tb1 - 2 - t)) {
-        case 2: wait_vmem<2 * DPW>(); break;
-        case 1: wait_vmem<DPW>(); break;
-        default: wait_vmem<0>(); break;
-      }
-      lds_barrier();
-      if (t + AHEAD < tb1) issue(t + AHEAD);
-    };
-    v4u fb[4], fa0[4];
-    switch (min(AHEAD - 1, tb1 - 1 - tb0)) {  // stage tb0 complete
-      case 3: wait_vmem<3 * DPW>(); break;
-      case 2: wait_vmem<2 * DPW>(); break;
-      case 1: wait_vmem<DPW>(); break;
-      default: wait_vmem<0>(); break;
-    }
-    lds_barrier();
-    read_b(tb0, fb);
-    read_a(tb0, 0, fa0);
-    // (fb, fa0) hold stage t's B and first A half on entry to each stage;
-    // two stages per trip with the fragment sets swapped, so no copies
-    int t = tb0;
-    for (; t + 2 < tb1; t += 2) {
-      v4u fa1[4], nb[4], na0[4];
-      read_a(t, 1, fa1);
-      mma_half(0, fa0, fb);
-      advance(t);
-      read_b(t + 1, nb);
-      read_a(t + 1, 0, na0);
-      mma_half(1, fa1, fb);
-      read_a(t + 1, 1, fa1);
-      mma_half(0, na0, nb);
-      advance(t + 1);
-      read_b(t + 2, fb);
-      read_a(t + 2, 0, fa0);
-      mma_half(1, fa1, nb);
-    }
-    if (t + 1 < tb1) {
-      v4u fa1[4], nb[4], na0[4];
-      read_a(t, 1, fa1);
-      mma_half(0, fa0, fb);
-      advance(t);
-      read_b(t + 1, nb);
-      read_a(t + 1, 0, na0);
-      mma_half(1, fa1, fb);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        fb[i] = nb[i];
-        fa0[i] = na0[i];
-      }
-      ++t;
-    }
-    {
-      v4u fa1[4];
-      read_a(tb1 - 1, 1, fa1);
-      mma_half(0, fa0, fb);
-      mma_half(1, fa1, fb);
-    }
-  } else {
-    for (int t = tb0; t < tb1; ++t) {
-      // stage t complete; the stages issued after it (up to NS - 2) may still be
-      // in flight
-      switch (min(NS - 2, tb1 - 1 - t)) {
-        case 3: wait_vmem<3 * DPW>(); break;
-        case 2: wait_vmem<2 * DPW>(); break;
-        case 1: wait_vmem<DPW>(); break;
-        default: wait_vmem<0>(); break;
-      }
-      lds_barrier();  // every wave's part of stage t has landed; stage t-1 is free
-      if (t + NS - 1 < tb1) issue(t + NS - 1);
-      const v4u* l_ = (const v4u*)(smem + ((t - tb0) % NS) * STAGE_B);
-#pragma unroll
-      for (int f = 0; f < MfmaOp<T>::kFrags; ++f) {
+      for (int f = 0; f < 2; ++f) {
         const int fo = (f * 4 + (lane >> 4)) * GT + (lane & 15);
         v4u bf[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) bf[b] = l_[fo + wj * 64 + b * 16];
+        for (int b = 0; b < 4; ++b) bf[b] = l_[CHUNKS + fo + wj * 64 + b * 16];
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
           v4u af[4];
 #pragma unroll
-          for (int a = 0; a < 4; ++a) af[a] = l_[CHUNKS + fo + wi * 128 + (4 * h2 + a) * 16];
+          for (int a = 0; a < 4; ++a) af[a] = l_[fo + wi * 128 + (4 * h2 + a) * 16];
 #pragma unroll
           for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) acc[4 * h2 + a][b] = MfmaOp<T>::mma(af[a], bf[b], acc[4 * h2 + a][b]);
-          if (HAS_LO && isg) {
-#pragma unroll
-            for (int a = 0; a < 4; ++a) af[a] = l_[2 * CHUNKS + fo + wi * 128 + (4 * h2 + a) * 16];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-              for (int b = 0; b < 4; ++b) acc[4 * h2 + a][b] = MfmaOp<T>::mma(af[a], bf[b], acc[4 * h2 + a][b]);
-          }
+            for (int b = 0; b < 4; ++b) acc[4 * h2 + a][b] = mma_f32(af[a], bf[b], acc[4 * h2 + a][b]);
         }
       }
     }
-  }
-
-  // epilogue.  Accumulator element r of block (a, b) sits at row
-  // 16a + 4*(lane/16) + r, column 16b + lane%16 of the wave's 128 x 64 part.
-  const int rq = (lane >> 4) * 4, cc = lane & 15;
-  float* C = isg ? A.G : A.H;
-  const int64_t ldc = isg ? A.ldg : A.ldh;
-  if (A.vec4) {
-    // Staged through the (now idle) LDS ring, one half tile (128 rows) at a
-    // time, so that every global access is a coalesced 16-byte one: the
-    // partial tile is stored, or the output read, added to and written back.
-    constexpr int LS = GT + 4;  // row stride of the staged rows, floats
-    constexpr int HR = 128 * LS * 4 <= NS * STAGE_B ? 128 : 64;  // rows per pass
-    static_assert(HR * LS * 4 <= NS * STAGE_B, "staging fits the ring");
-    float* st = (float*)smem;
-    __syncthreads();  // every wave is done with the ring
-#pragma unroll
-    for (int h = 0; h < GT / HR; ++h) {
-      if (wi == h * HR / 128)
-#pragma unroll
-        for (int a = 0; a < 8; ++a)
-          if (HR == 128 || a / 4 == h % 2)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                st[((a * 16) % HR + rq + r) * LS + wj * 64 + b * 16 + cc] = acc[a][b][r];
-      __syncthreads();
-#pragma unroll 4
-      for (int q = tid; q < HR * (GT / 4); q += 512) {
-        const int rr = q / (GT / 4), c4 = (q % (GT / 4)) * 4;
-        const float4 v = *(const float4*)&st[rr * LS + c4];
-        if (A.nseg > 1) {
-          float* base = A.part + ((int64_t)seg * A.ntiles + tile) * GT * GT;
-          *(float4*)&base[(h * HR + rr) * GT + c4] = v;
-        } else {
-          const int row = I * GT + h * HR + rr, col = J * GT + c4;
-          if (row < A.k && col < A.k) {
-            float4* cp = (float4*)(C + (int64_t)row * ldc + col);
-            float4 c = *cp;
-            c.x += v.x;
-            c.y += v.y;
-            c.z += v.z;
-            c.w += v.w;
-            *cp = c;
-          }
-        }
-      }
-      __syncthreads();
-    }
-    return;
-  }
-  if (A.nseg > 1) {
-    float* base = A.part + ((int64_t)seg * A.ntiles + tile) * GT * GT;
 #pragma unroll
     for (int a = 0; a < 8; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < 4; ++b) asm volatile("s_nop 1" : "+v"(acc[a][b]));  // the last products have been written
+    gram_store(A, isg, I, J, part, p0 == tb0, acc);
+    pp::lds_barrier();  // every wave is done with the stages
+    p0 = p1;
+  } while (p0 < tb1);
+}
+
+// bf16 inputs: the loop of pingpong.h over stages of 64 tokens (two token blocks;
+// the packing fills up the last pair with zeros).  The part of a wave, 128
+// columns x 64 rows, is split in halves of 64 columns and 32 rows; a unit of LDS is [token block][group]
+// [128 channels][16 bytes], filled from the packed operands in 1 KB pieces, and a
+// fragment read is linear in it (no bank conflicts).  Two streams: dX = hi + lo,
+// and a G tile takes both in turn for every 64 tokens (twice an H tile's stages).
+// Bound: MFMA issue and the clock under that load.  Measured, one chunk: 65536
+// tokens at k = 4096 1880 -> 1445 us; 8192 tokens, two streams, k = 11008 3360 -> 2150
+// us; 131072 at k = 28672 166 -> 137 ms (the form before had all eight waves in step on a ring of 32-token stages,
+// and gave four XCDs the H tiles and four the G tiles).
+constexpr int kGram16Unit = 128 * 128;  // bytes: 128 channels x 64 tokens
+constexpr size_t kGram16Lds = (size_t)8 * kGram16Unit;
+__global__ __launch_bounds__(512) void gram_bf16_kernel(GramArgs<uint16_t> A) {
+  constexpr int NG = kTokBlk / 8;
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // [stage parity][columns 0, 1, rows 0, 1]
+  int seg, part, tile, isg, I, J;
+  if (!gram_unit(A, &tile, &seg, &part)) return;
+  gram_tile(tile, A.nh, A.nt, A.g_full, &isg, &I, &J);
+  const int tb0 = seg * A.seg_len;  // even
+  const int ntb = (A.ntb + 1) / 2 * 2, tb1 = part < 0 ? ntb : min(ntb, tb0 + A.seg_len);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wi = wave >> 2, wj = wave & 3;
+  const int64_t tbs = (int64_t)NG * A.kp * 16;  // bytes per token block in a packed operand
+  const int sh = isg && A.Pl ? 1 : 0;           // two streams: hi and lo stages in turn
+  const int64_t lo_off = sh ? (const uint8_t*)A.Pl - (const uint8_t*)A.Pz : 0;
+  // Loads: wave w fills plane w of a unit (token block w / 4, group w % 4), 64 unit
+  // rows per load; unit row u is channel 128 (u / 64) + 64 h + u % 64 of the column tile
+  // J for half h, 64 (u / 32) + 32 h + u % 32 of the row tile I.  Everything but the lane's own
+  // 16 bytes is wave-uniform.
+  const int uw = __builtin_amdgcn_readfirstlane(wave);
+  const int64_t plane = (uw >> 2) * tbs + (int64_t)(uw & 3) * A.kp * 16;
+  const uint8_t* const ua = (const uint8_t*)A.Ph + plane + (int64_t)J * GT * 16;
+  const uint8_t* const ub = (const uint8_t*)(isg ? A.Pz : A.Ph) + plane + (int64_t)I * GT * 16;
+  const uint32_t la = lane * 16, lb = (64 * (lane >> 5) + (lane & 31)) * 16;
+  const uint32_t fa = (uint32_t)((lane >> 4) * 2048 + (wi * 64 + (lane & 15)) * 16);
+  const uint32_t fb = (uint32_t)((lane >> 4) * 2048 + (wj * 32 + (lane & 15)) * 16);
+  auto read_a = [&](int par, int h, u32x4 (&F)[2][4]) {
+    const uint8_t* p = smem + (par * 4 + h) * kGram16Unit + fa;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          base[(wi * 128 + a * 16 + rq + r) * GT + wj * 64 + b * 16 + cc] = acc[a][b][r];
-    return;
-  }
+    for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+      for (int a = 0; a < 4; ++a) F[s2][a] = *(const u32x4*)(p + s2 * 8192 + a * 256);
+  };
+  auto read_b = [&](int par, int h, u32x4 (&F)[2][2]) {
+    const uint8_t* p = smem + (par * 4 + 2 + h) * kGram16Unit + fb;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = I * GT + wi * 128 + a * 16 + rq + r, col = J * GT + wj * 64 + b * 16 + cc;
-        if (row < A.k && col < A.k) C[(int64_t)row * ldc + col] += acc[a][b][r];
-      }
+      for (int b = 0; b < 2; ++b) F[s2][b] = *(const u32x4*)(p + s2 * 8192 + b * 256);
+  };
+  int p0 = tb0;
+  do {  // pieces; an empty segment stores its zeros
+    const int p1 = min(tb1, p0 + A.piece);
+    f4 acc[8][4];
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+    if (p0 < p1) {  // uniform
+      const int nst = (p1 - p0) / 2 << sh;
+      const int64_t base = p0 * tbs;
+      auto issue = [&](int op, int st, int par) {
+        const int sc = min(st, nst - 1);
+        const int64_t off = base + (int64_t)(sc >> sh) * 2 * tbs + (op >= 2 && (sc & sh) ? lo_off : 0);
+        const uint8_t* u = op < 2 ? ua + off + op * 1024 : ub + off + (op - 2) * 512;
+        uint8_t* dst = smem + (par * 4 + op) * kGram16Unit + uw * 2048;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          __builtin_amdgcn_global_load_lds((const void*)(u + j * 2048 + (op < 2 ? la : lb)),
+                                           (__attribute__((address_space(3))) void*)(dst + j * 1024), 16, 0, 0);
+      };
+      pp::pp_loop<4, 2, 2>(nst, acc, issue, read_a, read_b);
+    }
+    gram_store(A, isg, I, J, part, p0 == tb0, acc);
+    pp::lds_barrier();  // every wave is done with the units
+    p0 = p1;
+  } while (p0 < tb1);
 }
 
 // Fixed-order sum of the per-segment partial tiles into H (upper tiles) and
@@ -1142,12 +1103,11 @@ __global__ __launch_bounds__(512) void gram_kernel(GramArgs<T> A) {
 // coalesced accesses.
 template <typename T>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(GramArgs<T> A) {
-  const int tile = blockIdx.x;
   int isg, I, J;
-  gram_tile(tile, A.nh, A.nt, A.g_full, &isg, &I, &J);
+  gram_tile(gram_order(A, A.ntiles - A.nsplit + (int)blockIdx.x), A.nh, A.nt, A.g_full, &isg, &I, &J);
   const int sr = (blockIdx.y >> 2) * 64, sc = (blockIdx.y & 3) * 64;
-  const int64_t stride = (int64_t)A.ntiles * GT * GT;
-  const float* p0 = A.part + (int64_t)tile * GT * GT;
+  const int64_t stride = (int64_t)A.nsplit * GT * GT;
+  const float* p0 = A.part + (int64_t)blockIdx.x * GT * GT;
   float* C = isg ? A.G : A.H;
   const int64_t ldc = isg ? A.ldg : A.ldh;
   if (A.vec4) {
@@ -1158,24 +1118,26 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(GramArgs<T> A) {
     float4 sum[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) sum[p] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // (nseg <= 8; segments past the last re-read the last one, and are not added)
-    float4 v[8][4];
+    // (eight segments at a time; those past the last re-read it, and are not added)
+    for (int s0 = 0; s0 < A.nseg; s0 += 8) {
+      float4 v[8][4];
 #pragma unroll
-    for (int sg = 0; sg < 8; ++sg)
+      for (int sg = 0; sg < 8; ++sg)
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        v[sg][p] = *(const float4*)(p0 + min(sg, A.nseg - 1) * stride + (sr + r0 + 16 * p) * GT + sc + c4);
+        for (int p = 0; p < 4; ++p)
+          v[sg][p] = *(const float4*)(p0 + min(s0 + sg, A.nseg - 1) * stride + (sr + r0 + 16 * p) * GT + sc + c4);
 #pragma unroll
-    for (int sg = 0; sg < 8; ++sg)
-      if (sg < A.nseg) {
+      for (int sg = 0; sg < 8; ++sg)
+        if (s0 + sg < A.nseg) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          sum[p].x += v[sg][p].x;
-          sum[p].y += v[sg][p].y;
-          sum[p].z += v[sg][p].z;
-          sum[p].w += v[sg][p].w;
+          for (int p = 0; p < 4; ++p) {
+            sum[p].x += v[sg][p].x;
+            sum[p].y += v[sg][p].y;
+            sum[p].z += v[sg][p].z;
+            sum[p].w += v[sg][p].w;
+          }
         }
-      }
+    }
     const int col = J * GT + sc + c4;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -1241,25 +1203,56 @@ int64_t hessian_chunk_tokens(int64_t m, int64_t k) {
   return m < ch ? (m < 1 ? 1 : m) : ch;
 }
 
-// Token segments per output tile: more segments fill the last wave of a
-// launch with too few tiles for 256 CUs, at the price of summing the partial
-// tiles afterwards.  Model: a full-length tile costs 2 * 256^2 * ch flop at
-// about 4.5 TFLOP/s per CU; the fixed-order sum of s partials reads s tiles
-// and reads and writes the output, (s + 2) * 256 KB per tile at about 4 TB/s.
-int gram_split(int64_t ntiles, int64_t ch, int64_t kp) {
-  (void)kp;
-  const double t_tile = 2.0 * GT * GT * (double)ch / 4.5e12;
+// Which tiles are split into token segments.  Whole rounds of 256 tiles (one per
+// CU) run unsplit; the rest of the tiles, or all of them when there is less than
+// one round, are split so that their segments fill the chip once more, at the
+// price of summing the partial tiles afterwards.  Model, per tile of `ch` tokens:
+// 2 * 256^2 * ch flop at 5.5 TFLOP/s (bf16) or 0.5 (fp32) per CU, 8 us of start
+// and epilogue per round; the sum of s partials reads s tiles and reads and
+// writes the output, (s + 2) * 256 KB at about 4 TB/s, and costs a launch (5 us).
+// `cost2`: two bf16 streams, where a G tile costs twice an H tile; the launch then
+// ends with the H tiles, and the split ones are the last of them.  At k = 4096, 65536
+// tokens (272 tiles) 16 tiles in 16 segments each: 1.06 rounds, where splitting
+// all tiles in 8 took 1.125 rounds and 310 us of sums per call.
+struct GramPlan {
+  int nsplit, nseg;
+};
+// Below one round (k <= 3840) the segments depend on k and the tokens alone (taken for
+// H and G's upper triangle), so that G has the same bits with and without H and
+// in either form.
+static GramPlan gram_plan(int64_t T, int64_t nh, int64_t ng, bool cost2, bool bf16, int64_t ch) {
+  const int64_t ntiles = nh + ng, work = ntiles + (cost2 ? ng : 0), both = T * (T + 1);
+  const bool small = both < 256;
+  const int64_t rest = small ? both : std::min(work % 256, ntiles);  // tiles to split
+  if (rest == 0) return {0, 1};
+  const double t_tile = 2.0 * GT * GT * (double)ch / (bf16 ? 5.5e12 : 0.5e12) * (small && cost2 ? 1.5 : 1.0);
   const double t_sum = (double)GT * GT * 4.0 / 4e12;
   int best = 1;
   double best_cost = 1e30;
-  for (int s = 1; s <= 8; ++s) {
-    const double cost = (double)cdiv(ntiles * s, 256) / s * t_tile + (s > 1 ? (double)ntiles * (s + 2) * t_sum : 0.0);
+  for (int s = 1; s <= 32; ++s) {
+    if (s > 1 && rest * s > 1024) break;
+    const double rounds = (double)cdiv(rest * s, 256);
+    const double cost = rounds / s * t_tile + rounds * 8e-6 + (s > 1 ? 5e-6 + (double)rest * (s + 2) * t_sum : 0.0);
     if (cost < best_cost * (1.0 - 1e-9)) {
       best_cost = cost;
       best = s;
     }
   }
-  return best;
+  return best > 1 ? GramPlan{(int)(small ? ntiles : rest), best} : GramPlan{0, 1};
+}
+
+// Tokens that one set of accumulators sums up: the products of a longer run are
+// added to H, G or the partial tile in pieces.  The relative error of the 32-bit
+// sums grows with the square root of the accumulation steps (32 tokens each in
+// bf16, 4 in fp32): measured 1.5e-6 in one piece of 65536 tokens (bf16, k = 4096),
+// 6.2e-7 in pieces of 16384, 4.4e-7 in pieces of 8192.  A piece costs a pass
+// over the output, whose rows lie further apart the larger k is, and takes the
+// workgroups of an XCD out of step: 25 us at k = 4096 (390 us of products per 16384
+// tokens), 140 us at k = 28672 (131072 tokens: 137 ms in one piece, 152 in pieces of
+// 16384, 167 of 8192).
+static int gram_piece(int64_t k, bool bf16) {
+  const int t = k <= 9216 ? 16384 : k <= 20480 ? 24576 : 131072;
+  return (bf16 ? t : k <= 9216 ? 4096 : 8192) / kTokBlk;
 }
 
 // Diagonal of H in fp64 for act_order: hdiag[c] += sum_t Xh[t][c]^2, read
@@ -1329,10 +1322,14 @@ static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   const int64_t kp = rup(k, GT);
   const int64_t tokp = rup(ch, 256);
   const int64_t T = kp / GT;
-  // partial tiles: enough for either G form (all of G, or its upper triangle)
-  const int64_t nt_full = T * (T + 1) / 2 + T * T, nt_up = T * (T + 1);
-  const int64_t part_tiles = std::max(gram_split(nt_full, ch, kp) > 1 ? gram_split(nt_full, ch, kp) * nt_full : 0,
-                                      gram_split(nt_up, ch, kp) > 1 ? gram_split(nt_up, ch, kp) * nt_up : 0);
+  // partial tiles: enough for every form (with and without H; all of G, its upper
+  // triangle or none; one stream or two; either dtype)
+  int64_t part_tiles = 0;
+  for (int f = 0; f < 24; ++f) {
+    const int64_t up = T * (T + 1) / 2, nh = f & 1 ? up : 0, ng = f / 8 == 0 ? 0 : f / 8 == 1 ? up : T * T;
+    const GramPlan p = gram_plan(T, nh, ng, f & 2, f & 4, ch);
+    part_tiles = std::max(part_tiles, (int64_t)p.nsplit * (p.nseg > 1 ? p.nseg : 0));
+  }
   Carver c(ws);
   HessWs h;
   h.flags = c.take<uint32_t>(64);
@@ -1358,18 +1355,18 @@ duo_status hessian_status_run(const void* ws, hipStream_t s) {
   return f ? DUO_ERR_NONFINITE : DUO_OK;
 }
 
-template <typename T, bool LO>
+template <typename T>
 static duo_status launch_gram(const GramArgs<T>& A, hipStream_t s) {
-  constexpr int NOP = LO ? 3 : 2;
-  const size_t stage = NOP * (size_t)GT * kTokBlk * sizeof(T);
-  const size_t ns = (160 * 1024) / stage < 5 ? (160 * 1024) / stage : 5;
-  const size_t lds = ns * stage;
-  auto kern = gram_kernel<T, LO, false>;
-  if constexpr (sizeof(T) == 2 && !LO)
-    if (A.nseg > 1) kern = gram_kernel<T, LO, true>;  // tokens split into segments: shallow ring
-  DUO_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  const int grid = (int)rup((int64_t)A.ntiles * A.nseg, 8);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, s, A);
+  const int64_t nfull = A.ntiles - A.nsplit;
+  const int64_t n1 = A.mixed ? std::min<int64_t>(A.ntiles - A.nh, nfull) : nfull;
+  const dim3 grid((unsigned)(8 * (cdiv(n1, 8) + cdiv(nfull - n1, 8) + cdiv((int64_t)A.nsplit * A.nseg, 8))));
+  if constexpr (sizeof(T) == 2) {
+    if (duo_status st = set_max_lds((const void*)gram_bf16_kernel, kGram16Lds); st != DUO_OK) return st;
+    hipLaunchKernelGGL(gram_bf16_kernel, grid, dim3(512), kGram16Lds, s, A);
+  } else {
+    if (duo_status st = set_max_lds((const void*)gram_f32_kernel, 2 * kGram32Stage); st != DUO_OK) return st;
+    hipLaunchKernelGGL(gram_f32_kernel, grid, dim3(512), 2 * kGram32Stage, s, A);
+  }
   DUO_LAUNCH_CHECK();
   return DUO_OK;
 }
@@ -1387,7 +1384,7 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
   const int nt = (int)(kp / GT);
   const int nh_all = nt * (nt + 1) / 2;
   const int ng = want_g ? (g_full ? nt * nt : nh_all) : 0;
-  const int nseg = gram_split((want_h ? nh_all : 0) + ng, ch, kp);  // within what the workspace was sized for
+  const GramPlan plan = gram_plan(nt, want_h ? nh_all : 0, ng, lo, sizeof(T) == 2, ch);  // as the workspace was sized for
   hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, s, w.flags);
   DUO_LAUNCH_CHECK();
   for (int64_t t0 = 0; t0 < m; t0 += ch) {
@@ -1442,16 +1439,19 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
     GramArgs<T> A;
     A.Ph = (const T*)w.Ph;
     A.Pz = (const T*)w.Pz;
-    A.Pl = (const T*)w.Pl;
+    A.Pl = lo ? (const T*)w.Pl : nullptr;
     A.kp = (int)kp;
     A.k = (int)k;
     A.nt = nt;
     A.nh = want_h ? nh_all : 0;
     A.ntiles = A.nh + ng;
     A.g_full = g_full;
-    A.nseg = nseg;
+    A.piece = gram_piece(k, sizeof(T) == 2);
+    A.mixed = lo;
+    A.nsplit = plan.nsplit;
+    A.nseg = plan.nseg;
     A.ntb = (int)cdiv(mc, kTokBlk);
-    A.seg_len = (int)cdiv(A.ntb, nseg);
+    A.seg_len = (int)rup(cdiv(A.ntb, A.nseg), 2);  // whole stages of 64 tokens (bf16)
     A.H = H;
     A.ldh = ldh;
     A.G = G;
@@ -1462,14 +1462,11 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
       A.vec4 = k % 4 == 0 && (!want_h || (ldh % 4 == 0 && al16(H))) && (!want_g || (ldg % 4 == 0 && al16(G)));
     }
     prof_begin(DUO_PROF_GRAM, s);
-    if constexpr (sizeof(T) == 2)
-      st = lo ? launch_gram<T, true>(A, s) : launch_gram<T, false>(A, s);
-    else
-      st = launch_gram<T, false>(A, s);
+    st = launch_gram<T>(A, s);
     prof_end(DUO_PROF_GRAM, s);
     if (st != DUO_OK) return st;
-    if (nseg > 1) {
-      hipLaunchKernelGGL(gram_reduce_kernel<T>, dim3(A.ntiles, (GT / 64) * (GT / 64)), dim3(256), 0, s, A);
+    if (A.nsplit > 0) {
+      hipLaunchKernelGGL(gram_reduce_kernel<T>, dim3(A.nsplit, (GT / 64) * (GT / 64)), dim3(256), 0, s, A);
       DUO_LAUNCH_CHECK();
     }
   }
