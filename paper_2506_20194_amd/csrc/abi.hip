@@ -3,6 +3,7 @@
 // anything is enqueued.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -52,6 +53,9 @@ PruneWs carve_prune(void* ws, int64_t n, int64_t k, int B) {
   w.bytes = c.off;
   return w;
 }
+
+// packed operands of the split products of duo_prune_layer, after carve_prune's part
+size_t prune_pk_bytes(int64_t n, int64_t k, int B) { return std::max(score_pk_bytes(k), sweep_pk_bytes(n, k, B)); }
 
 bool k_ok(int64_t k) { return k >= 1 && k <= kMaxK; }
 
@@ -115,13 +119,13 @@ size_t duo_workspace_size(int32_t op, int64_t n, int64_t k, int64_t m, int32_t b
   switch (op) {
     case DUO_OP_HESSIAN: return hessian_ws_bytes(m < 1 ? 1 : m, k);
     case DUO_OP_CHOL_INV: return chol_ws_bytes(k);
-    case DUO_OP_SCORE_TERMS: return score_ws_bytes(k);
+    case DUO_OP_SCORE_TERMS: return score_ws_bytes(k) + score_pk_bytes(k);
     case DUO_OP_SWEEP:
       if (n < 1 || block < 1 || block > kMaxBlock) return 0;
       return sweep_ws_bytes(n, k, block);
     case DUO_OP_PRUNE_LAYER:
       if (n < 1 || block < 1 || block > kMaxBlock) return 0;
-      return carve_prune(nullptr, n, k, block).bytes;
+      return carve_prune(nullptr, n, k, block).bytes + prune_pk_bytes(n, k, block);
     default: return 0;
   }
 }
@@ -209,13 +213,13 @@ duo_status duo_chol_inv(float* H_inout, int64_t k, int64_t ldh, double damp_rati
                         size_t ws_bytes, void* stream) {
   if (!H_inout || ldh < k || !std::isfinite(damp_ratio) || damp_ratio < 0.0) return DUO_ERR_INVALID_ARG;
   if (!k_ok(k)) return k < 1 ? DUO_ERR_INVALID_ARG : DUO_ERR_UNSUPPORTED;
-  if (!ws_ok(ws, ws_bytes, chol_ws_bytes(k))) return DUO_ERR_WORKSPACE;
+  if (!ws_ok(ws, ws_bytes, chol_ws_bytes(k, false))) return DUO_ERR_WORKSPACE;
   duo_status d = device_ok();
   if (d != DUO_OK) return d;
   CholStatus* st = nullptr;
   const hipStream_t s = (hipStream_t)stream;
   prof_begin(DUO_PROF_CHOL, s);
-  duo_status r = chol_run(H_inout, k, ldh, damp_ratio, ws, s, &st);
+  duo_status r = chol_run(H_inout, k, ldh, damp_ratio, ws, ws_bytes, s, &st);
   prof_end(DUO_PROF_CHOL, s);
   if (r != DUO_OK) return r;
   if (!info) return DUO_OK;
@@ -237,7 +241,9 @@ duo_status duo_score_terms(const float* L, int64_t ldl, const float* G, int64_t 
   duo_status d = device_ok();
   if (d != DUO_OK) return d;
   prof_begin(DUO_PROF_SCORE, (hipStream_t)stream);
-  duo_status r = score_run(L, ldl, G, ldg, a, k, D, ldd, fac, ws, (hipStream_t)stream);
+  const size_t base = score_ws_bytes(k);
+  duo_status r = score_run(L, ldl, G, ldg, a, k, D, ldd, fac, ws, (uint8_t*)ws + base, ws_bytes - base,
+                           (hipStream_t)stream);
   prof_end(DUO_PROF_SCORE, (hipStream_t)stream);
   return r;
 }
@@ -276,7 +282,7 @@ duo_status duo_sweep(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
   if (d != DUO_OK) return d;
   prof_begin(DUO_PROF_SWEEP, (hipStream_t)stream);
   duo_status r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, D, ldd, fac, w_sparsity, o, block, mask_in, W_out,
-                           W_out_lowp, mask_out, block_scores_out, ws, (hipStream_t)stream);
+                           W_out_lowp, mask_out, block_scores_out, ws, nullptr, 0, (hipStream_t)stream);
   prof_end(DUO_PROF_SWEEP, (hipStream_t)stream);
   return r;
 }
@@ -307,17 +313,19 @@ duo_status duo_prune_layer(const void* W, int32_t w_dtype, int64_t n, int64_t k,
   // k^3 / 3 of D but launches two more products per block (measured at
   // n = k = 4096: 0.17 ms slower per layer; k = 11008: 2 ms faster).
   const bool yform = o.form == DUO_FORM_Y || (o.form == DUO_FORM_AUTO && y_ok && k >= kYFormMinK);
+  void* const pk = (uint8_t*)ws + pw.bytes;
+  const size_t pk_bytes = ws_bytes - pw.bytes;
   prof_begin(DUO_PROF_SCORE, s);
-  duo_status r = score_run(L, ldl, G, ldg, a, k, yform ? nullptr : w.D, k, w.fac, w.score, s);
+  duo_status r = score_run(L, ldl, G, ldg, a, k, yform ? nullptr : w.D, k, w.fac, w.score, pk, pk_bytes, s);
   prof_end(DUO_PROF_SCORE, s);
   if (r != DUO_OK) return r;
   prof_begin(DUO_PROF_SWEEP, s);
   if (yform)
     r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, nullptr, 0, w.fac, w_sparsity, o, block, mask_in, W_out, W_out_lowp,
-                  mask_out, block_scores_out, w.sweep, s, score_u(w.score, k), k, w.D);
+                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s, score_u(w.score, k), k, w.D);
   else
     r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, w.D, k, w.fac, w_sparsity, o, block, mask_in, W_out, W_out_lowp,
-                  mask_out, block_scores_out, w.sweep, s);
+                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s);
   prof_end(DUO_PROF_SWEEP, s);
   return r;
 }

@@ -28,6 +28,10 @@ duo_status set_max_lds(const void* fn, size_t bytes);
 // kept iff ((magnitude bits of x) << 32 | c) > thr[t]; z entries are zeroed.
 duo_status act_threshold_run(const void* X, int32_t dtype, int64_t m, int64_t k, int64_t ldx, int z, int64_t* thr,
                              hipStream_t s);
+// The same rule applied: Y = X with the dropped entries zero, for rows of X and Y
+// that 16-byte accesses can take (else *done is false and nothing is enqueued).
+duo_status act_sparsify_run(const uint16_t* X, int64_t m, int64_t k, int64_t ldx, int z, uint16_t* Y, int64_t ldy,
+                            bool* done, hipStream_t s);
 duo_status act_mask_run(const void* X, int32_t dtype, int64_t m, int64_t k, int64_t ldx, int z, uint32_t* mask,
                         void* ws, hipStream_t s);
 
@@ -84,6 +88,19 @@ enum { ORDER_XCD = 0, ORDER_PLAIN = 1, ORDER_DIAG = 2 };
 
 duo_status gemm_f32(const GemmDesc& d, hipStream_t s);
 
+// ---- fp32 products on the bf16 matrix cores (split.hip) ----
+// gemm_f32 for products large enough to gain from it, else gemm_f32 itself.  pk:
+// scratch for the packed operands, split_bytes(M, N, K, products) of the largest
+// product (dual and batched ones: their number); with less, gemm_f32 runs.
+// With TRI_UPPER, C's diagonal 256 x 256 tiles are written whole.
+// zero_a, zero_b: entries of a one-term product's operands that count as zero
+// whatever is stored there (the tiles are 256 wide, and inside a 256-wide diagonal
+// tile the 128-wide block below (above) the diagonal need not hold zeros).
+enum { ZERO_NONE = 0, ZERO_BELOW = 1, ZERO_UPTO = 2, ZERO_ABOVE = 3 };  // l < r, l <= r, l > r (r: i of A, j of B)
+size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products);
+duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s, int zero_a = ZERO_NONE,
+                          int zero_b = ZERO_NONE);
+
 // ---- stage 2 (chol.hip) ----
 struct CholStatus {
   double lambda;
@@ -91,20 +108,25 @@ struct CholStatus {
   int status;
   int pad;
 };
-size_t chol_ws_bytes(int64_t k);
-duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, hipStream_t s,
+// full = false: without the packed operands of the split products
+size_t chol_ws_bytes(int64_t k, bool full = true);
+duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, size_t ws_bytes, hipStream_t s,
                     CholStatus** status_dev);
 
 // ---- stage 3 (score.hip, sweep.hip) ----
+// Scratch of the split products (packed operands) comes as pk, pk_bytes; without
+// it the fp32 instructions do the work.
 size_t score_ws_bytes(int64_t k);
+size_t score_pk_bytes(int64_t k);
 // D = NULL: Q, fac only (no D = U L^T); U (the upper 128-tiles of Q with the
 // entries on and below the diagonal zeroed, k x k, ld k) stays in the
 // workspace, at score_u(ws, k).
 duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k,
-                     float* D, int64_t ldd, float* fac, void* ws, hipStream_t s);
+                     float* D, int64_t ldd, float* fac, void* ws, void* pk, size_t pk_bytes, hipStream_t s);
 const float* score_u(const void* ws, int64_t k);
 
 size_t sweep_ws_bytes(int64_t n, int64_t k, int B);
+size_t sweep_pk_bytes(int64_t n, int64_t k, int B);  // of the Y form
 // Sweep options (validated by the caller).  nm_n > 0: the N:4 variant (nm_n
 // of every 4 consecutive columns of a row pruned, chosen when the sweep reaches
 // the group; p_w unused).  q_bits > 0: joint RTN quantisation with one grid per
@@ -124,7 +146,7 @@ struct SweepOpts {
 duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64_t ldw, const float* L,
                      int64_t ldl, const float* D, int64_t ldd, const float* fac, double p_w, const SweepOpts& o, int B,
                      const uint32_t* mask_in, float* W_out, void* W_out_lowp, uint32_t* mask_out,
-                     float* scores_out, void* ws, hipStream_t s, const float* U = nullptr, int64_t ldu = 0,
-                     float* Y = nullptr);
+                     float* scores_out, void* ws, void* pk, size_t pk_bytes, hipStream_t s,
+                     const float* U = nullptr, int64_t ldu = 0, float* Y = nullptr);
 
 }  // namespace duo

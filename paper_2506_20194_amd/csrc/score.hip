@@ -58,11 +58,12 @@ ScoreWs carve(void* ws, int64_t k) {
 }  // namespace
 
 size_t score_ws_bytes(int64_t k) { return carve(nullptr, k).bytes; }
+size_t score_pk_bytes(int64_t k) { return split_bytes(k, k, k, 1); }
 
 const float* score_u(const void* ws, int64_t k) { return carve(const_cast<void*>(ws), k).Q; }
 
 duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k, float* D,
-                     int64_t ldd, float* fac, void* ws, hipStream_t s) {
+                     int64_t ldd, float* fac, void* ws, void* pk, size_t pk_bytes, hipStream_t s) {
   const ScoreWs w = carve(ws, k);
   // Q = G L on upper tiles; L[l][i] = 0 for l < i, so l starts at the tile column
   GemmDesc q{};
@@ -75,7 +76,7 @@ duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, c
   q.order = ORDER_PLAIN;  // K range [j0, k): the first columns are the longest
   q.nterms = 1;
   q.t[0] = GemmTerm{G, ldg, 1, L, ldl, 1, (int)k, 1.f, KLO_COL, KHI_FULL};
-  duo_status st = gemm_f32(q, s);
+  duo_status st = gemm_f32_split(q, pk, pk_bytes, s, ZERO_BELOW, ZERO_BELOW);  // G's upper triangle, L's lower
   if (st != DUO_OK) return st;
   hipLaunchKernelGGL(fac_kernel, dim3((unsigned)k), dim3(256), 0, s, w.Q, (int64_t)k, L, ldl, a, (int)k, fac);
   DUO_LAUNCH_CHECK();
@@ -91,7 +92,7 @@ duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, c
   d.order = ORDER_DIAG;  // K range [i0, j0 + 128): grows with the distance from the diagonal
   d.nterms = 1;
   d.t[0] = GemmTerm{w.Q, k, 1, L, ldl, 0, (int)k, 1.f, KLO_ROW, KHI_COL};
-  return gemm_f32(d, s);
+  return gemm_f32_split(d, pk, pk_bytes, s, ZERO_UPTO);  // U is strictly upper
 }
 
 }  // namespace duo

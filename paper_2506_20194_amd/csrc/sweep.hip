@@ -950,11 +950,12 @@ SweepWs carve(void* ws, int64_t n, int64_t k, int B) {
 }  // namespace
 
 size_t sweep_ws_bytes(int64_t n, int64_t k, int B) { return carve(nullptr, n, k, B).bytes; }
+size_t sweep_pk_bytes(int64_t n, int64_t k, int B) { return split_bytes(n, k, super_width(B), 2); }
 
 duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64_t ldw, const float* L, int64_t ldl,
                      const float* D, int64_t ldd, const float* fac, double p_w, const SweepOpts& o, int B,
                      const uint32_t* mask_in, float* W_out, void* W_out_lowp, uint32_t* mask_out, float* scores_out,
-                     void* ws, hipStream_t s, const float* U, int64_t ldu, float* Y) {
+                     void* ws, void* pk, size_t pk_bytes, hipStream_t s, const float* U, int64_t ldu, float* Y) {
   const SweepWs w = carve(ws, n, k, B);
   const bool yr = U != nullptr;  // Y form
   // the Y form with quantisation: only grids fixed at a block's first column,
@@ -1092,7 +1093,7 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
         g.t[0] = GemmTerm{w.EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, 1.f, KLO_ZERO, KHI_FULL};
         g.t[1] = GemmTerm{w.EW + S + (u0 - sb0), 2 * S, 1, U + u0 * ldu + c0, ldu, 1, K, 1.f, KLO_ZERO, KHI_FULL};
         prof_begin(DUO_PROF_TRAIL, s);
-        duo_status st = gemm_f32(g, s);
+        duo_status st = gemm_f32_split(g, pk, pk_bytes, s);
         prof_end(DUO_PROF_TRAIL, s);
         if (st != DUO_OK) return st;
       } else {
