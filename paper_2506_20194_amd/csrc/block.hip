@@ -52,32 +52,6 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* __restrict
   for (int c = threadIdx.x; c < d; c += 256) y[c] = f32_to_bf16_bits(ld_bf16(x + c) * inv);
 }
 
-// 16-byte form (k, ldx, ldy multiples of 8, aligned rows): one workgroup row
-// of threads per token, 8 channels per thread.
-__global__ __launch_bounds__(256) void act_apply8_kernel(const uint16_t* __restrict__ X, int64_t ldx, int k,
-                                                         const int64_t* __restrict__ thr, uint16_t* __restrict__ Y,
-                                                         int64_t ldy) {
-  const int cpr = (k + 2047) / 2048;  // workgroups per token
-  const int t = (int)(blockIdx.x / cpr);
-  const int c0 = ((int)(blockIdx.x % cpr) * 256 + threadIdx.x) * 8;
-  if (c0 >= k) return;
-  const int64_t th = thr[t];
-  const u32x4 x = *(const u32x4*)(X + (int64_t)t * ldx + c0);
-  u32x4 y;
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    uint32_t o = 0;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t v = (x[h] >> (16 * j)) & 0xFFFFu;
-      const int64_t key = ((int64_t)(v & 0x7fffu) << 32) | (c0 + 2 * h + j);
-      o |= (key > th ? v : 0u) << (16 * j);
-    }
-    y[h] = o;
-  }
-  *(u32x4*)(Y + (int64_t)t * ldy + c0) = y;
-}
-
 __global__ void act_apply_kernel(const uint16_t* __restrict__ X, int64_t ldx, int m, int k,
                                  const int64_t* __restrict__ thr, uint16_t* __restrict__ Y, int64_t ldy) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -696,16 +670,15 @@ duo_status duo_act_sparsify(const void* X, int64_t m, int64_t k, int64_t ldx, du
   if (!ws || ws_bytes < need || !aligned(ws)) return DUO_ERR_WORKSPACE;
   if (duo_status d = device_ok(); d != DUO_OK) return d;
   hipStream_t s = (hipStream_t)stream;
+  bool done;
+  duo_status st = act_sparsify_run((const uint16_t*)X, m, k, ldx, act_zeros(rule, k), (uint16_t*)Y, ldy, &done, s);
+  if (st != DUO_OK || done) return st;
   int64_t* thr = (int64_t*)ws;
-  duo_status st = act_threshold_run(X, DUO_BF16, m, k, ldx, act_zeros(rule, k), thr, s);
+  st = act_threshold_run(X, DUO_BF16, m, k, ldx, act_zeros(rule, k), thr, s);
   if (st != DUO_OK) return st;
   const int64_t tot = m * k;
-  if (k % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 && aligned16(X) && aligned16(Y) && m * cdiv(k, 2048) <= INT32_MAX)
-    hipLaunchKernelGGL(act_apply8_kernel, dim3((unsigned)(m * cdiv(k, 2048))), dim3(256), 0, s,
-                       (const uint16_t*)X, ldx, (int)k, (const int64_t*)thr, (uint16_t*)Y, ldy);
-  else
-    hipLaunchKernelGGL(act_apply_kernel, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, s, (const uint16_t*)X, ldx,
-                       (int)m, (int)k, (const int64_t*)thr, (uint16_t*)Y, ldy);
+  hipLaunchKernelGGL(act_apply_kernel, dim3((unsigned)cdiv(tot, 256)), dim3(256), 0, s, (const uint16_t*)X, ldx,
+                     (int)m, (int)k, (const int64_t*)thr, (uint16_t*)Y, ldy);
   DUO_LAUNCH_CHECK();
   return DUO_OK;
 }
