@@ -17,6 +17,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -202,14 +203,63 @@ __device__ inline void load_mags(const T* __restrict__ x, int k, int c0, uint32_
 }
 
 // bf16 magnitudes (15 bits): Tm = the z-th smallest (1 <= z < the number of
-// valid entries) and the number below it, from one LDS histogram of all 32768
+// valid entries) and the number below it, from two LDS histograms: the top 10
+// bits (bin t is thread t's: one read and one block scan), then the low 5 bits of
+// the z-th entry's bin.  (One histogram of all 32768 magnitudes has 132 KB to
+// clear and 32 bins per thread to scan; with more than 16384 entries that is less
+// than the waits of the atomics on the fewer coarse bins: k = 28672 45.1 us per
+// token with the one histogram, 46.7 with the two; k = 4096 19.9 and 14.8.)
+constexpr int kFineBits = 5, kCoarse = 1 << (15 - kFineBits), kFine = 1 << kFineBits;
+static_assert(kCoarse == kGemvThreads, "one coarse bin per thread");
+
+template <int KPT>
+__device__ inline void hist_select(const uint32_t (&mag)[KPT], int z, uint32_t* hist, int* found, uint32_t* sh,
+                                   uint32_t& Tm, int& nbelow) {
+  const int t = threadIdx.x;
+  hist[t] = 0u;
+  if (t < kFine) hist[kCoarse + t] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < KPT; ++e)
+    if (mag[e] < 32768u) atomicAdd(&hist[mag[e] >> kFineBits], 1u);
+  __syncthreads();
+  const uint32_t cnt = hist[t];
+  uint32_t tot;
+  const uint32_t before = block_excl_scan(cnt, sh, tot);
+  if ((int)before < z && z <= (int)(before + cnt)) {  // one thread
+    found[0] = t;
+    found[1] = (int)before;
+  }
+  __syncthreads();
+  const uint32_t cb = (uint32_t)found[0];
+  const int below = found[1];
+#pragma unroll
+  for (int e = 0; e < KPT; ++e)
+    if ((mag[e] >> kFineBits) == cb) atomicAdd(&hist[kCoarse + (mag[e] & (kFine - 1u))], 1u);
+  __syncthreads();
+  // every wave scans the 32 fine bins for itself
+  const int lane = t & 63;
+  const int f = lane < kFine ? (int)hist[kCoarse + lane] : 0;
+  int incl = f;
+#pragma unroll
+  for (int d = 1; d < kFine; d <<= 1) {
+    const int o = __shfl_up(incl, d);
+    if (lane >= d) incl += o;
+  }
+  const int run = below + incl - f;
+  const int src = __builtin_ctzll(__ballot(run < z && z <= run + f));
+  Tm = (cb << kFineBits) | (uint32_t)src;
+  nbelow = __shfl(run, src);
+}
+
+// The same for more than 16384 channels, from one LDS histogram of all 32768
 // magnitudes (one atomic per entry; bin b at word b + b / 32, so that thread
 // t's 32 bins [32 t, 32 t + 32) sit 33 words from its neighbours' and the
 // scan's reads are free of bank conflicts) and a block scan of the bins.
 constexpr int kHistWords = 32768 + 32768 / 32;
 
 template <int KPT>
-__device__ inline void hist_select(const uint32_t (&mag)[KPT], int z, uint32_t* hist, int* found, uint32_t* sh,
+__device__ inline void hist_select_full(const uint32_t (&mag)[KPT], int z, uint32_t* hist, int* found, uint32_t* sh,
                                    uint32_t& Tm, int& nbelow) {
   const int t = threadIdx.x;
   for (int q = t; q < kHistWords / 4; q += kGemvThreads) ((u32x4*)hist)[q] = u32x4{0u, 0u, 0u, 0u};
@@ -310,14 +360,16 @@ struct DscSlab {
   uint32_t base, xbits, a0;
 };
 
-template <typename T>
+// KPT: channels per thread in the selection (k <= 1024 KPT).  With 32 for every k, a
+// layer of 4096 channels kept 128 of the 1024 threads busy (decode of 4096 x 4096:
+// 19.9 us per token, now 14.8).
+template <typename T, int KPT>
 __global__ __launch_bounds__(kGemvThreads) void dsc_gemv_kernel(const T* __restrict__ x, int k, int z, int64_t n,
                                                                 const int64_t* __restrict__ col_ptr,
                                                                 const uint32_t* __restrict__ maskT,
                                                                 const uint16_t* __restrict__ chunk_off,
                                                                 const uint16_t* __restrict__ values, int S, int cap,
                                                                 float* __restrict__ ypart) {
-  constexpr int KPT = kMaxK / kGemvThreads;  // channels per thread in the selection: 32
   constexpr int MB = sizeof(T) == 2 ? 15 : 31;  // magnitude bits
   extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
   __shared__ uint32_t hist[256];
@@ -338,7 +390,9 @@ __global__ __launch_bounds__(kGemvThreads) void dsc_gemv_kernel(const T* __restr
   uint32_t Tm = z >= k ? 0xffffffffu : 0u;  // z = 0: everything kept; z >= k: nothing
   int nbelow = 0;
   if (z > 0 && z < k) {
-    if constexpr (MB == 15)
+    if constexpr (MB == 15 && KPT > 16)
+      hist_select_full<KPT>(mag, z, (uint32_t*)dyn, found, scan_sh, Tm, nbelow);
+    else if constexpr (MB == 15)
       hist_select<KPT>(mag, z, (uint32_t*)dyn, found, scan_sh, Tm, nbelow);
     else
       radix_select<MB, KPT>(mag, z, hist, found, Tm, nbelow);
@@ -531,7 +585,7 @@ struct GemvPlan {
   size_t lds;
 };
 
-GemvPlan gemv_plan(int64_t n, int na) {
+GemvPlan gemv_plan(int64_t n, int64_t k, int na) {
   GemvPlan p;
   p.ns = (int)cdiv(n, kSlabRows);
   const int per = kTargetGroups / p.ns > 0 ? kTargetGroups / p.ns : 1;
@@ -539,7 +593,8 @@ GemvPlan gemv_plan(int64_t n, int na) {
   p.cap = (na + p.S - 1) / p.S;
   const size_t a = 16 * (size_t)p.cap + (size_t)kGemvWaves * (kSlotQ + 1) * 16;
   p.lds = a > kRedBytes ? a : kRedBytes;
-  if (p.lds < kHistWords * sizeof(uint32_t)) p.lds = kHistWords * sizeof(uint32_t);  // the bf16 selection's histogram
+  // the selection's histogram of all magnitudes (bf16, KPT > 16)
+  if (k > 16 * kGemvThreads && p.lds < kHistWords * sizeof(uint32_t)) p.lds = kHistWords * sizeof(uint32_t);
   return p;
 }
 
@@ -568,17 +623,22 @@ duo_status gemv_launch(const void* x, int32_t x_dtype, int64_t n, int64_t k, duo
                        const int64_t* col_ptr, const uint32_t* maskT, const uint16_t* chunk_off,
                        const uint16_t* values, float* y, float* ypart, hipStream_t s) {
   const int z = rule.kind == DUO_ACT_NONE ? 0 : (int)floor(rule.sparsity * (double)k + 0.5);
-  const GemvPlan p = gemv_plan(n, (int)(k - z));  // the rule keeps exactly k - z channels
-  const void* kern = x_dtype == DUO_BF16 ? (const void*)dsc_gemv_kernel<uint16_t> : (const void*)dsc_gemv_kernel<float>;
-  if (duo_status d = set_max_lds(kern, p.lds); d != DUO_OK) return d;
-  prof_begin(DUO_PROF_DECODE, s);
-  if (x_dtype == DUO_BF16)
-    hipLaunchKernelGGL(dsc_gemv_kernel<uint16_t>, dim3((unsigned)(p.ns * p.S)), dim3(kGemvThreads), p.lds, s,
-                       (const uint16_t*)x, (int)k, z, n, col_ptr, maskT, chunk_off, values, p.S, p.cap, ypart);
-  else
-    hipLaunchKernelGGL(dsc_gemv_kernel<float>, dim3((unsigned)(p.ns * p.S)), dim3(kGemvThreads), p.lds, s,
-                       (const float*)x, (int)k, z, n, col_ptr, maskT, chunk_off, values, p.S, p.cap, ypart);
-  DUO_LAUNCH_CHECK();
+  const GemvPlan p = gemv_plan(n, k, (int)(k - z));  // the rule keeps exactly k - z channels
+  auto go = [&](auto kern, auto xp) -> duo_status {
+    if (duo_status d = set_max_lds((const void*)kern, p.lds); d != DUO_OK) return d;
+    prof_begin(DUO_PROF_DECODE, s);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.ns * p.S)), dim3(kGemvThreads), p.lds, s, xp, (int)k, z, n, col_ptr, maskT,
+                       chunk_off, values, p.S, p.cap, ypart);
+    DUO_LAUNCH_CHECK();
+    return DUO_OK;
+  };
+  auto pick = [&](auto xp) -> duo_status {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(xp)>>;
+    if (k <= 8 * kGemvThreads) return go(dsc_gemv_kernel<T, 8>, xp);
+    if (k <= 16 * kGemvThreads) return go(dsc_gemv_kernel<T, 16>, xp);
+    return go(dsc_gemv_kernel<T, 32>, xp);
+  };
+  if (duo_status d = x_dtype == DUO_BF16 ? pick((const uint16_t*)x) : pick((const float*)x); d != DUO_OK) return d;
   prof_end(DUO_PROF_DECODE, s);
   hipLaunchKernelGGL(dsc_reduce_kernel, dim3((unsigned)cdiv(n, 64)), dim3(1024), 0, s, (const float*)ypart, n, p.S, y);
   DUO_LAUNCH_CHECK();
@@ -670,7 +730,7 @@ duo_status duo_dsc_gemv_noalloc(const void* x, int32_t x_dtype, int64_t n, int64
   if (duo_status d = gemv_check(x, x_dtype, n, k, rule, col_ptr, maskT, chunk_off, values, y); d != DUO_OK) return d;
   if (duo_status d = device_ok(); d != DUO_OK) return d;
   const int z = rule.kind == DUO_ACT_NONE ? 0 : (int)floor(rule.sparsity * (double)k + 0.5);
-  const GemvPlan p = gemv_plan(n, (int)(k - z));
+  const GemvPlan p = gemv_plan(n, k, (int)(k - z));
   if ((size_t)p.S * (size_t)n > kScratchFloats) return DUO_ERR_UNSUPPORTED;
   float* part = nullptr;
   if (duo_status d = scratch_address(&part); d != DUO_OK) return d;
