@@ -583,17 +583,18 @@ __global__ void act_mask_kernel(const T* __restrict__ X, int64_t ldx, int m, int
 }
 
 // ---------------------------------------------------------------------------
-// pack: 256 channels x 256 tokens per workgroup, in 8 tiles of 32 tokens.
+// pack: 256 channels x tpb tiles of 32 tokens per workgroup.
 // Packed layout (EPG = 16 / sizeof(T) elements per group, NG = 32 / EPG):
 //   P[((tb * NG + g) * kp + c) * EPG + e]  = value of token tb*32 + g*EPG + e.
-// apart[tokens/256 block][kp] receives per-channel partial sums of dX^2.
+// A workgroup takes tpb blocks of 32 tokens (pack_blocks); apart[workgroup row][kp]
+// receives per-channel partial sums of dX^2.
 // ---------------------------------------------------------------------------
 template <typename T, bool TWO>
 __global__ __launch_bounds__(256) void pack_kernel(const T* __restrict__ Xs, const T* __restrict__ Xd,
                                                    int64_t ldx, int mc, int k, int kp,
                                                    const int64_t* __restrict__ thr, T* __restrict__ Ph,
                                                    T* __restrict__ Pz, T* __restrict__ Pl,
-                                                   float* __restrict__ apart) {
+                                                   float* __restrict__ apart, int tpb) {
   constexpr int EPG = 16 / (int)sizeof(T);
   constexpr int NG = kTokBlk / EPG;
   constexpr bool LO = TWO && sizeof(T) == 2;  // bf16 two-stream: dX = hi + lo
@@ -608,7 +609,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* __restrict__ Xs, con
   float* sa = (float*)raw;  // reused after the token loop
 
   const int cb0 = blockIdx.x * 256;
-  const int tsb = blockIdx.y * 256;
+  const int tsb = blockIdx.y * tpb * kTokBlk;
   const int tr = threadIdx.x >> 3;        // token row inside a 32-token tile
   const int cg = (threadIdx.x & 7) * 32;  // first of 32 channels
   const T zero = Elem<T>::from_f32(0.f);
@@ -616,7 +617,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* __restrict__ Xs, con
 #pragma unroll
   for (int e = 0; e < 32; ++e) acc[e] = 0.f;
 
-  for (int tt = 0; tt < 8; ++tt) {
+  for (int tt = 0; tt < tpb; ++tt) {
     const int tok0 = tsb + tt * kTokBlk;
     if (tok0 >= (int)rup(mc, 2 * kTokBlk)) break;  // uniform; zeros fill up the last pair of token blocks
     const int t = tok0 + tr;
@@ -673,7 +674,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* __restrict__ Xs, con
 }
 
 // bf16 pack (16-byte aligned rows, k % 8 == 0).  Workgroup (x, y) covers
-// channels [512x, 512x + 512) of tokens [256y, 256y + 256): wave w handles
+// channels [512x, 512x + 512) of token blocks [tpb y, tpb (y + 1)): wave w handles
 // tokens 8w..8w+7 of every 32-token block, lane l channels 512x + 8l .. +7.
 // Each lane loads its 8 x 8 tile with 16-byte reads, applies the threshold in
 // registers and transposes it (tokens become the contiguous dimension): one
@@ -689,7 +690,7 @@ __global__ __launch_bounds__(256) void pack16_kernel(const uint16_t* __restrict_
                                                      int64_t ldx, int mc, int k, int kp,
                                                      const int64_t* __restrict__ thr, uint16_t* __restrict__ Ph,
                                                      uint16_t* __restrict__ Pz, uint16_t* __restrict__ Pl,
-                                                     float* __restrict__ apart) {
+                                                     float* __restrict__ apart, int tpb) {
   __shared__ float red[4][512];
   __shared__ u32x4 stg[4][576];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -698,8 +699,8 @@ __global__ __launch_bounds__(256) void pack16_kernel(const uint16_t* __restrict_
   float acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-  for (int tt = 0; tt < 8; ++tt) {
-    const int tb = blockIdx.y * 8 + tt;
+  for (int tt = 0; tt < tpb; ++tt) {
+    const int tb = blockIdx.y * tpb + tt;
     if (tb * kTokBlk >= (int)rup(mc, 2 * kTokBlk)) break;  // uniform; zeros fill up the last pair of token blocks
     const int tbase = tb * kTokBlk + 8 * wave;
     u32x4 xs[8], xd[8];
@@ -1389,6 +1390,17 @@ static int diag_slices(int64_t kp, int ntb) {
   return n < 1 ? 1 : (int)n;
 }
 
+// Token blocks per packing workgroup: eight, or fewer where that leaves CUs idle
+// (2048 x 512 fp32 in 16 workgroups of eight 56 us; with one block each the whole layer is 60 us
+// shorter).
+static int pack_blocks(int64_t mc, int64_t kp) {
+  const int64_t wg = kp / 256 * cdiv(mc, 256);
+  return wg >= 512 ? 8 : wg >= 128 ? 2 : 1;
+}
+// partial sums of a: a row per workgroup row, at most 2^20 floats where those are
+// more than one per 256 tokens (128 workgroups of 8 blocks at most, or 512 of 2)
+constexpr int64_t kApartMin = int64_t(1) << 20;
+
 static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   const int64_t ch = hessian_chunk_tokens(m, k);
   const int64_t kp = rup(k, GT);
@@ -1409,7 +1421,7 @@ static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   h.Ph = c.take<uint8_t>((size_t)tokp * kp * 4);  // sized for fp32; bf16 uses half
   h.Pz = c.take<uint8_t>((size_t)tokp * kp * 4);
   h.Pl = c.take<uint8_t>((size_t)tokp * kp * 2);  // low part exists for bf16 only
-  h.apart = c.take<float>((size_t)(tokp / 256) * kp);
+  h.apart = c.take<float>((size_t)std::max((tokp / 256) * kp, kApartMin));
   h.part = c.take<float>(part_tiles > 0 ? (size_t)part_tiles * GT * GT : 1);
   h.dpart = c.take<double>((size_t)diag_slices(kp, kDiagSlices) * kp);
   h.bytes = c.off;
@@ -1469,27 +1481,28 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
       st = launch_act_select<T>(xd, ldx, mc, (int)k, 0, w.thr + rup(ch, 256), w.flags, s);
       if (st != DUO_OK) return st;
     }
-    dim3 pg((unsigned)(kp / 256), (unsigned)cdiv(mc, 256));
+    const int tpb = pack_blocks(mc, kp), prow = (int)cdiv(rup(mc, 2 * kTokBlk) / kTokBlk, tpb);
+    dim3 pg((unsigned)(kp / 256), (unsigned)prow);
     if constexpr (sizeof(T) == 2) {
       if (bf16_vec_ok(xs, ldx, k) && (!two || bf16_vec_ok(xd, ldx, k))) {
-        dim3 pg16((unsigned)cdiv(kp, 512), (unsigned)cdiv(mc, 256));
+        dim3 pg16((unsigned)cdiv(kp, 512), (unsigned)prow);
         if (two)
           hipLaunchKernelGGL(pack16_kernel<true>, pg16, dim3(256), 0, s, (const uint16_t*)xs, (const uint16_t*)xd,
                              ldx, mc, (int)k, (int)kp, w.thr, (uint16_t*)w.Ph, (uint16_t*)w.Pz, (uint16_t*)w.Pl,
-                             want_g ? w.apart : nullptr);
+                             want_g ? w.apart : nullptr, tpb);
         else
           hipLaunchKernelGGL(pack16_kernel<false>, pg16, dim3(256), 0, s, (const uint16_t*)xs, (const uint16_t*)xs,
                              ldx, mc, (int)k, (int)kp, w.thr, (uint16_t*)w.Ph, (uint16_t*)w.Pz, (uint16_t*)w.Pl,
-                             want_g ? w.apart : nullptr);
+                             want_g ? w.apart : nullptr, tpb);
         goto packed;
       }
     }
     if (two)
       hipLaunchKernelGGL((pack_kernel<T, true>), pg, dim3(256), 0, s, xs, xd, ldx, mc, (int)k, (int)kp, w.thr,
-                         (T*)w.Ph, (T*)w.Pz, (T*)w.Pl, want_g ? w.apart : nullptr);
+                         (T*)w.Ph, (T*)w.Pz, (T*)w.Pl, want_g ? w.apart : nullptr, tpb);
     else
       hipLaunchKernelGGL((pack_kernel<T, false>), pg, dim3(256), 0, s, xs, xs, ldx, mc, (int)k, (int)kp, w.thr,
-                         (T*)w.Ph, (T*)w.Pz, (T*)w.Pl, want_g ? w.apart : nullptr);
+                         (T*)w.Ph, (T*)w.Pz, (T*)w.Pl, want_g ? w.apart : nullptr, tpb);
   packed:
     DUO_LAUNCH_CHECK();
     if (hdiag) {
@@ -1504,7 +1517,7 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
       DUO_LAUNCH_CHECK();
     }
     if (want_g) {
-      hipLaunchKernelGGL(a_reduce_kernel, dim3((unsigned)cdiv(k, 32)), dim3(256), 0, s, w.apart, (int)cdiv(mc, 256),
+      hipLaunchKernelGGL(a_reduce_kernel, dim3((unsigned)cdiv(k, 32)), dim3(256), 0, s, w.apart, prow,
                          (int)kp, (int)k, a);
       DUO_LAUNCH_CHECK();
     }
