@@ -22,9 +22,14 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_FP32_TFLOPS = 157.3    # MI355X dense fp32 MFMA
+# Large fp32 products run as six bf16 products of exactly split operands: from this
+# k up most of the factorisation, score and lazy-update flop do, and their rates are
+# priced against a sixth of the bf16 peak
+SPLIT_MIN_K = 7168
+PEAK_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 
-# Bytes from beyond L2 per gram_kernel launch on this workload, from rocprofv3
+# Bytes from beyond L2 per gram_bf16_kernel launch on this workload, from rocprofv3
 # --pmc FETCH_SIZE and WRITE_SIZE runs (profiles/gram_kernel_llama2_70b_down_proj_hbm_traffic.md),
 # each scaled by what the same counter reads for a plain 1 GiB streaming kernel
 # (FETCH_SIZE x2.0, WRITE_SIZE x1.0).  Valid only for the kernel source they
@@ -488,6 +493,7 @@ def main():
     # inverse, Cholesky, full products) and is printed beside it
     chol_score_flop = (3 if yform else 4) * k ** 3 / 3
     chol_score_flop_plain = 8 * k ** 3 / 3
+    f32_peak = PEAK_SPLIT_TFLOPS if k >= SPLIT_MIN_K else PEAK_FP32_TFLOPS
     # the Gram kernel multiplies in the calibration input's precision: bf16
     # MFMA for bf16 inputs, fp32 MFMA for fp32 inputs
     gram_peak = PEAK_BF16_TFLOPS if c["x_dtype"] == torch.bfloat16 else PEAK_FP32_TFLOPS
@@ -510,17 +516,18 @@ def main():
                    "mask": f"{args.nm}:4" if args.nm else "unstructured",
                    "quant": f"int{args.quant} g128" if args.quant else None,
                    "residual_form": "Y" if yform else "D", "parallelism": "single GPU"},
-        "roofline": {"bound": "mfma", "kernel": "gram_kernel (H, G)", "achieved": gram_tflops,
-                     "peak": gram_peak, "unit": "TFLOP/s", "frac": gram_tflops / gram_peak,
+        "roofline": {"bound": "mfma", "kernel": f"gram_{'bf16' if gram_peak == PEAK_BF16_TFLOPS else 'f32'}_kernel (H, G)",
+                     "achieved": gram_tflops, "peak": gram_peak, "unit": "TFLOP/s", "frac": gram_tflops / gram_peak,
                      "traffic": gram_traffic(args.workload), "ms_per_launch": per("gram"), "flop_per_launch": gram_flop_step / gram_launches},
         "hessian_tflops": hess_tflops,
         "hessian_frac": hess_tflops / gram_peak,
         "sweep_gbs": sweep_gbs,
         "sweep_frac": sweep_gbs / PEAK_HBM_GBS,
         "trailing_tflops": trail_tflops,
-        "trailing_frac": trail_tflops / PEAK_FP32_TFLOPS,
+        "trailing_frac": trail_tflops / f32_peak,
         "chol_score_tflops": chol_score_flop / ((per_step("chol") + per_step("score")) * 1e-3) / 1e12,
-        "chol_score_frac": chol_score_flop / ((per_step("chol") + per_step("score")) * 1e-3) / 1e12 / PEAK_FP32_TFLOPS,
+        "chol_score_frac": chol_score_flop / ((per_step("chol") + per_step("score")) * 1e-3) / 1e12 / f32_peak,
+        "fp32_product_peak_TFLOPs": f32_peak,
         "chol_score_flop_count": ("k^3 (implemented route, Y form: no D)" if yform else "(4/3) k^3 (implemented route)")
                                  + "; plain route (8/3) k^3 gives "
                                  f"{chol_score_flop_plain / ((per_step('chol') + per_step('score')) * 1e-3) / 1e12:.1f} TFLOP/s",

@@ -3,15 +3,17 @@
 // a = diag(dX dX^T) (paper Sec. 4.2-4.3, Algorithm 1 first lines).
 //
 // Pipeline per chunk of tokens:
-//   act_select  one workgroup per token finds the largest dropped key
-//               (|x|, channel) by bisection on the magnitude bits;
+//   act_select  finds each token's largest dropped key (|x|, channel) by a
+//               search on the magnitude bits (one wave or one workgroup per
+//               token; the same kernels can write the sparsified row);
 //   pack        applies the per-token threshold and writes Xh and dX (and,
 //               for two input streams, the low part of dX) in an MFMA-ready
 //               token-blocked layout [token block][group][channel][16 bytes];
 //               also sums dX^2 per channel;
-//   gram        MFMA kernel over pairs of 128-channel tiles (i >= j): one
-//               pass over the tokens yields H_ij, G_ij and G_ji;
-//   reductions  fixed-order sums of per-segment partials (deterministic).
+//   gram        gram_bf16_kernel (256 x 128 tiles) or gram_f32_kernel over the
+//               tiles at and below the diagonal: one pass over the tokens
+//               yields H_ij, G_ij and G_ji;
+//   reductions  fixed-order sums of the partial tiles (deterministic).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
