@@ -73,7 +73,8 @@ __global__ __launch_bounds__(256) void damp_kernel(float* H, int64_t ldh, int k,
 //   leaf     one wave factors A_JJ = V_JJ V_JJ^T and inverts it in the same
 //            sweep (column c of the working matrix drives both the rank-1
 //            update of the columns before it and the back substitution
-//            V N = I of the columns after it), as rank-1 MFMA updates with no
+//            V N = I of the columns after it); column c reaches the wave's
+//            lanes as scalars read from its lane, so the 32 steps need no
 //            LDS round trip and no workgroup barrier;
 //   panel    V_IJ = A_IJ N_JJ^T for the leaves I < J, and beside it the
 //            finished inverse blocks N_JK = -N_JJ T_JK for K > J;
@@ -89,7 +90,6 @@ __global__ __launch_bounds__(256) void damp_kernel(float* H, int64_t ldh, int k,
 // Padding rows/columns beyond s are an identity block.
 constexpr int DS = kTile + 2;  // LDS row stride of the working matrices (rows 2 banks apart)
 constexpr int LF = 32;         // leaf width
-typedef float f16v __attribute__((ext_vector_type(16)));
 
 // acc(32x32) += A(32x32) * op(B)(32x32) for one wave on fp32 MFMA
 // (16x16x4): lane l supplies A[16a + l%16][k + l/16] and op(B)[k + l/16][16b +
@@ -128,40 +128,42 @@ __device__ inline void store32(float* C, const f4 (&acc)[2][2], int lane, float 
       }
 }
 
-// Step c of the leaf sweep, as two rank-1 updates on v_mfma_f32_32x32x2_f32.  The
-// wave holds the working matrix W and the inverse N (N = I at first) as accumulators:
-// element r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.  Row c
-// sits in one register of one half of the lanes; the leading c x c block of W is
-// symmetric, so that register, cut to the columns below c, is the rows' operand as
-// well (in the k slot of its half, zeros in the other), and
-//   W[i][q] -= W[c][i] W[c][q] / W[c][c],  N[i][q] -= W[c][i] N[c][q] / W[c][c]   (i < c);
-// then row c of N is final but for its factor 1 / sqrt(W[c][c]).  The chain per step
-// is one MFMA (64 cycles), the pivot's read and reciprocal root; N's MFMA runs in
-// its shadow.  (With W's columns in lanes and 3c vector instructions per step a
-// leaf took 12.5k cycles and diag_factor_kernel 34-35 us; now 27 us.)
+// Step c of the leaf sweep.  Lane q (and its twin q + 32, which repeats the
+// same work) holds column q of the 32 x 32 working matrix in x[0..31].  Column
+// c reaches every lane as scalars read from lane c, so a step needs no LDS
+// round trip and no barrier.  The leading c x c block stays symmetric (every
+// update to it is a symmetric rank-1 term), so the coefficient W[q][c] of a
+// column q < c is the lane's own W[c][q]; for q > c (the columns that become
+// the inverse) it is W[c][q] by definition.
 template <int C>
-__device__ __forceinline__ void leaf_step(f16v& W, f16v& N, int lane, int& fail) {
-  constexpr int HC = (C >> 2) & 1, RC = (C >> 3) * 4 + (C & 3);
-  const bool mine = (lane >> 5) == HC;
-  const float v = W[RC], nv = N[RC];
-  const float piv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32 * HC + C));
+__device__ __forceinline__ void leaf_step(float (&x)[LF], int q, int& fail) {
+  // the lane's column made opaque per step, so that the compiler evaluates
+  // the lane tests where they are used instead of hoisting (and spilling)
+  // the masks of every step out of the leaf loop
+  asm volatile("" : "+v"(q));
+  float cv[C > 0 ? C : 1];
+#pragma unroll
+  for (int i = 0; i < C; ++i)
+    cv[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[i]), C));
+  const float piv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[C]), C));
   if (!(piv > 0.f) && fail < 0) fail = C;  // uniform
   const float inv = __builtin_amdgcn_rsqf(piv);
   const float inv2 = inv * inv;
-  if constexpr (C > 0) {
-    const float a = mine && (lane & 31) < C ? v : 0.f;
-    W = __builtin_amdgcn_mfma_f32_32x32x2f32(a, -(a * inv2), W, 0, 0, 0);
-    const float bn = mine ? -(nv * inv2) : 0.f;
-    N[RC] = mine ? nv * inv : nv;
-    N = __builtin_amdgcn_mfma_f32_32x32x2f32(a, bn, N, 0, 0, 0);
-  } else {
-    N[RC] = mine ? nv * inv : nv;
+  const float xc = x[C];
+  const float coef = xc * inv2;
+#pragma unroll
+  for (int i = 0; i < C; ++i) x[i] = fmaf(-cv[i], coef, x[i]);
+  if (q == C) {
+    // the pivot column: rows below the diagonal are never read again
+#pragma unroll
+    for (int i = 0; i < C; ++i) x[i] = -cv[i] * inv2;
   }
+  x[C] = q == C ? inv : (q > C ? xc * inv : xc);
 }
 
 template <int... Cs>
-__device__ __forceinline__ void leaf_steps(f16v& W, f16v& N, int lane, int& fail, std::integer_sequence<int, Cs...>) {
-  (leaf_step<LF - 1 - Cs>(W, N, lane, fail), ...);
+__device__ __forceinline__ void leaf_steps(float (&x)[LF], int q, int& fail, std::integer_sequence<int, Cs...>) {
+  (leaf_step<LF - 1 - Cs>(x, q, fail), ...);
 }
 
 __global__ __launch_bounds__(256) void diag_factor_kernel(const float* H, int64_t ldh, int r0, int s, float* vinv,
@@ -207,18 +209,15 @@ __global__ __launch_bounds__(256) void diag_factor_kernel(const float* H, int64_
     const int j0 = J * LF;
     const int q = lane & (LF - 1);
     int fail = -1;
-    f16v x, nv;
+    float x[LF];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      x[r] = A[(j0 + i) * DS + j0 + q];
-      nv[r] = i == q ? 1.f : 0.f;
-    }
-    leaf_steps(x, nv, lane, fail, std::make_integer_sequence<int, LF>{});
+    for (int i = 0; i < LF; ++i) x[i] = A[(j0 + i) * DS + j0 + q];
+    leaf_steps(x, q, fail, std::make_integer_sequence<int, LF>{});
+    if (lane < LF) {
+      int qs = q;
+      asm volatile("" : "+v"(qs));  // no hoisted per-row masks
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      N[(j0 + i) * DS + j0 + q] = i <= q ? nv[r] : 0.f;
+      for (int i = 0; i < LF; ++i) N[(j0 + i) * DS + j0 + qs] = i <= qs ? x[i] : 0.f;
     }
     if (lane == 0 && fail >= 0 && *fail_sh < 0) *fail_sh = j0 + fail;
   };
