@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libduo.so")
-SOURCES = ["abi.hip", "hessian.hip", "gemm_f32.hip", "split.hip", "pad.hip", "chol.hip", "score.hip", "sweep.hip", "profile.hip",
+SOURCES = ["abi.hip", "hessian.hip", "gemm_f32.hip", "split.hip", "chol.hip", "score.hip", "sweep.hip", "profile.hip",
            "block.hip", "permute.hip", "decode.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -54,41 +54,8 @@ PruneWs carve_prune(void* ws, int64_t n, int64_t k, int B) {
   return w;
 }
 
-// Padded operands of a layer whose n or k is no multiple of 64 (none otherwise),
-// after carve_prune's part: L, G (then D), Q, Y, the working matrix and the errors at
-// np x kp, both multiples of 64.  n = 1500, k = 3000 with INT4 groups (inverse factor
-// and layer): 3.37 ms on edge tiles with bounds checks per element, 2.90 here.
-struct PrunePad {
-  float *L, *G, *Q, *Y;
-  SweepPad sweep;
-  int64_t kp;
-  size_t bytes;
-};
-
-PrunePad carve_pad(void* ws, int64_t n, int64_t k, int B) {
-  PrunePad p{};
-  if (n % 64 == 0 && k % 64 == 0) return p;
-  Carver c(ws);
-  p.kp = k % 64 ? rup(k, kTile) : k;
-  p.sweep.np = rup(n, kTile);
-  p.sweep.ldo = p.kp;
-  if (p.kp != k) {  // else L, G and D need no copy
-    p.L = c.take<float>((size_t)p.kp * p.kp);
-    p.G = c.take<float>((size_t)p.kp * p.kp);
-    p.Q = c.take<float>((size_t)p.kp * p.kp);
-  }
-  p.Y = c.take<float>((size_t)p.sweep.np * p.kp);
-  p.sweep.Wk = c.take<float>((size_t)p.sweep.np * p.kp);
-  p.sweep.EW = c.take<float>((size_t)p.sweep.np * 2 * super_width(B));
-  p.bytes = c.off;
-  return p;
-}
-
-// packed operands of the split products of duo_prune_layer, after those parts
-size_t prune_pk_bytes(int64_t n, int64_t k, int B) {
-  const int64_t kp = k % 64 ? rup(k, kTile) : k;
-  return std::max(score_pk_bytes(kp), sweep_pk_bytes(rup(n, kTile), kp, B));
-}
+// packed operands of the split products of duo_prune_layer, after carve_prune's part
+size_t prune_pk_bytes(int64_t n, int64_t k, int B) { return std::max(score_pk_bytes(k), sweep_pk_bytes(n, k, B)); }
 
 bool k_ok(int64_t k) { return k >= 1 && k <= kMaxK; }
 
@@ -158,8 +125,7 @@ size_t duo_workspace_size(int32_t op, int64_t n, int64_t k, int64_t m, int32_t b
       return sweep_ws_bytes(n, k, block);
     case DUO_OP_PRUNE_LAYER:
       if (n < 1 || block < 1 || block > kMaxBlock) return 0;
-      return carve_prune(nullptr, n, k, block).bytes + carve_pad(nullptr, n, k, block).bytes +
-             prune_pk_bytes(n, k, block);
+      return carve_prune(nullptr, n, k, block).bytes + prune_pk_bytes(n, k, block);
     default: return 0;
   }
 }
@@ -276,7 +242,7 @@ duo_status duo_score_terms(const float* L, int64_t ldl, const float* G, int64_t 
   if (d != DUO_OK) return d;
   prof_begin(DUO_PROF_SCORE, (hipStream_t)stream);
   const size_t base = score_ws_bytes(k);
-  duo_status r = score_run(L, ldl, G, ldg, a, k, k, D, ldd, fac, (float*)ws, (uint8_t*)ws + base, ws_bytes - base,
+  duo_status r = score_run(L, ldl, G, ldg, a, k, D, ldd, fac, ws, (uint8_t*)ws + base, ws_bytes - base,
                            (hipStream_t)stream);
   prof_end(DUO_PROF_SCORE, (hipStream_t)stream);
   return r;
@@ -347,38 +313,19 @@ duo_status duo_prune_layer(const void* W, int32_t w_dtype, int64_t n, int64_t k,
   // k^3 / 3 of D but launches two more products per block (measured at
   // n = k = 4096: 0.17 ms slower per layer; k = 11008: 2 ms faster).
   const bool yform = o.form == DUO_FORM_Y || (o.form == DUO_FORM_AUTO && y_ok && k >= kYFormMinK);
-  PrunePad pd = carve_pad((uint8_t*)ws + pw.bytes, n, k, block);
-  const bool padded = pd.bytes > 0 && ws_bytes >= pw.bytes + pd.bytes;
-  if (!padded) pd.bytes = 0;
-  void* const pk = (uint8_t*)ws + pw.bytes + pd.bytes;
-  const size_t pk_bytes = ws_bytes - pw.bytes - pd.bytes;
-  int64_t kp = k;
-  float *Q = (float*)w.score, *D = w.D, *Y = w.D;
+  void* const pk = (uint8_t*)ws + pw.bytes;
+  const size_t pk_bytes = ws_bytes - pw.bytes;
   prof_begin(DUO_PROF_SCORE, s);
-  if (padded) {
-    Y = pd.Y;
-    if (pd.kp != k) {
-      kp = pd.kp;
-      if (duo_status e2 = pad_copy(L, ldl, k, k, pd.L, kp, kp, kp, 0.f, s); e2 != DUO_OK) return e2;
-      if (duo_status e2 = pad_copy(G, ldg, k, k, pd.G, kp, kp, kp, 0.f, s); e2 != DUO_OK) return e2;
-      L = pd.L;
-      G = pd.G;
-      ldl = ldg = kp;
-      Q = pd.Q;
-      D = pd.G;  // G is not read any more when D is formed
-    }
-  }
-  duo_status r = score_run(L, ldl, G, ldg, a, k, kp, yform ? nullptr : D, kp, w.fac, Q, pk, pk_bytes, s);
+  duo_status r = score_run(L, ldl, G, ldg, a, k, yform ? nullptr : w.D, k, w.fac, w.score, pk, pk_bytes, s);
   prof_end(DUO_PROF_SCORE, s);
   if (r != DUO_OK) return r;
   prof_begin(DUO_PROF_SWEEP, s);
-  const SweepPad* const sp = padded ? &pd.sweep : nullptr;
   if (yform)
     r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, nullptr, 0, w.fac, w_sparsity, o, block, mask_in, W_out, W_out_lowp,
-                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s, Q, kp, Y, sp);
+                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s, score_u(w.score, k), k, w.D);
   else
-    r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, D, kp, w.fac, w_sparsity, o, block, mask_in, W_out, W_out_lowp,
-                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s, nullptr, 0, nullptr, sp);
+    r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, w.D, k, w.fac, w_sparsity, o, block, mask_in, W_out, W_out_lowp,
+                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s);
   prof_end(DUO_PROF_SWEEP, s);
   return r;
 }

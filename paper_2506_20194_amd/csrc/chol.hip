@@ -315,9 +315,7 @@ __global__ __launch_bounds__(256) void place_diag_kernel(float* H, int64_t ldh, 
 }
 
 // L = N^T: tile pair (ti <= tj): upper tile (ti, tj) -> lower tile (tj, ti); upper zeroed.
-// (N in V's place, or in a padded copy: then the zeros above the diagonal go to H
-// in the same way)
-__global__ __launch_bounds__(256) void transpose_upper_kernel(float* H, int64_t ldh, int k, const float* N, int64_t ldn) {
+__global__ __launch_bounds__(256) void transpose_upper_kernel(float* H, int64_t ldh, int k) {
   __shared__ float t[64][65];
   int ti, tj;
   tri_pair(blockIdx.x, &tj, &ti);  // ti <= tj, tiles of 64
@@ -326,7 +324,7 @@ __global__ __launch_bounds__(256) void transpose_upper_kernel(float* H, int64_t 
     const int r = e / 64, c = e % 64;
     const int gi = i0 + r, gj = j0 + c;
     float v = 0.f;
-    if (gi < k && gj < k && gi <= gj) v = N[(int64_t)gi * ldn + gj];
+    if (gi < k && gj < k && gi <= gj) v = H[(int64_t)gi * ldh + gj];
     t[r][c] = v;
   }
   __syncthreads();
@@ -447,38 +445,20 @@ static size_t chol_pk_bytes(int64_t k) {
   return b;
 }
 
-// The padded copy of a matrix whose size is no multiple of 64.
-static size_t chol_pad_bytes(int64_t k) {
-  return k % 64 ? align_up((size_t)rup(k, kTile) * rup(k, kTile) * sizeof(float)) : 0;
-}
-
-size_t chol_ws_bytes(int64_t k, bool full) {
-  return carve(nullptr, k).bytes + (full ? chol_pad_bytes(k) + chol_pk_bytes(rup(k, k % 64 ? kTile : 1)) : 0);
-}
+size_t chol_ws_bytes(int64_t k, bool full) { return carve(nullptr, k).bytes + (full ? chol_pk_bytes(k) : 0); }
 
 constexpr size_t kDiagLds = (size_t)(2 * kTile * DS + 4) * sizeof(float);
 
-duo_status chol_run(float* H0, int64_t k0, int64_t ldh0, double damp, void* ws, size_t ws_bytes, hipStream_t s,
+duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, size_t ws_bytes, hipStream_t s,
                     CholStatus** status_dev) {
-  const CholWs w = carve(ws, k0);
-  // A matrix that the aligned products do not take is factored in a copy padded
-  // to whole 128-blocks with an identity (the factorisation starts at that end and
-  // the identity is coupled to nothing, so the rest is what it would be in place):
-  // with n = 1500 and INT4 groups, k = 3000 took 3.37 ms in place (both stages, on edge
-  // tiles with bounds checks per element), 2.90 in copies.
-  const size_t pad = chol_pad_bytes(k0);
-  const bool padded = pad > 0 && ws_bytes >= w.bytes + pad;
-  const int64_t k = padded ? rup(k0, kTile) : k0, ldh = padded ? k : ldh0;
-  float* const H = padded ? (float*)((uint8_t*)ws + w.bytes) : H0;
-  void* const pk = (uint8_t*)ws + w.bytes + (padded ? pad : 0);
-  const size_t pk_bytes = ws_bytes - w.bytes - (padded ? pad : 0);
+  const CholWs w = carve(ws, k);
+  void* const pk = (uint8_t*)ws + w.bytes;
+  const size_t pk_bytes = ws_bytes - w.bytes;
   if (duo_status d = set_max_lds((const void*)diag_factor_kernel, kDiagLds); d != DUO_OK) return d;
   *status_dev = w.st;
   const int T = (int)cdiv(k, kTile);
-  hipLaunchKernelGGL(damp_kernel, dim3(1), dim3(256), 0, s, H0, ldh0, (int)k0, damp, w.st);
+  hipLaunchKernelGGL(damp_kernel, dim3(1), dim3(256), 0, s, H, ldh, (int)k, damp, w.st);
   DUO_LAUNCH_CHECK();
-  if (padded)
-    if (duo_status d = pad_copy(H0, ldh0, k0, k0, H, k, k, k, 1.f, s); d != DUO_OK) return d;
   auto factor = [&](int b, int sz) -> duo_status {
     const int r0 = b * kTile;
     hipLaunchKernelGGL(diag_factor_kernel, dim3(1), dim3(256), kDiagLds, s, (const float*)H, ldh, r0, sz,
@@ -555,9 +535,8 @@ duo_status chol_run(float* H0, int64_t k0, int64_t ldh0, double damp, void* ws, 
   DUO_LAUNCH_CHECK();
   duo_status st = trinv(H, ldh, k, T, w.X, pk, pk_bytes, s);
   if (st != DUO_OK) return st;
-  const int T64 = (int)cdiv(k0, 64);
-  hipLaunchKernelGGL(transpose_upper_kernel, dim3(T64 * (T64 + 1) / 2), dim3(256), 0, s, H0, ldh0, (int)k0,
-                     (const float*)H, ldh);
+  const int T64 = (int)cdiv(k, 64);
+  hipLaunchKernelGGL(transpose_upper_kernel, dim3(T64 * (T64 + 1) / 2), dim3(256), 0, s, H, ldh, (int)k);
   DUO_LAUNCH_CHECK();
   return DUO_OK;
 }

@@ -101,11 +101,6 @@ size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products);
 duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s, int zero_a = ZERO_NONE,
                           int zero_b = ZERO_NONE);
 
-// dst (rows_p x cols_p, ld ldd, 16-byte aligned rows) = src (rows x cols) with zeros
-// around it, and `diag` on the diagonal past the rows.  (pad.hip)
-duo_status pad_copy(const float* src, int64_t lds, int64_t rows, int64_t cols, float* dst, int64_t ldd, int64_t rows_p,
-                    int64_t cols_p, float diag, hipStream_t s);
-
 // ---- stage 2 (chol.hip) ----
 struct CholStatus {
   double lambda;
@@ -124,11 +119,11 @@ duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, siz
 size_t score_ws_bytes(int64_t k);
 size_t score_pk_bytes(int64_t k);
 // D = NULL: Q, fac only (no D = U L^T); U (the upper 128-tiles of Q with the
-// entries on and below the diagonal zeroed) stays in Q, ld kp.
-// kp >= k: the size that L, G, D and Q are computed at (k, or zero-padded to kp by
-// the caller).  Q: k_p x k_p scratch, U's place afterwards.
-duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k, int64_t kp,
-                     float* D, int64_t ldd, float* fac, float* Q, void* pk, size_t pk_bytes, hipStream_t s);
+// entries on and below the diagonal zeroed, k x k, ld k) stays in the
+// workspace, at score_u(ws, k).
+duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k,
+                     float* D, int64_t ldd, float* fac, void* ws, void* pk, size_t pk_bytes, hipStream_t s);
+const float* score_u(const void* ws, int64_t k);
 
 size_t sweep_ws_bytes(int64_t n, int64_t k, int B);
 size_t sweep_pk_bytes(int64_t n, int64_t k, int B);  // of the Y form
@@ -148,20 +143,10 @@ struct SweepOpts {
 // U != NULL: the Y form (no D; D ignored): U is the strictly upper part of Q
 // (only entries U[i][j] with j > i are read, on 128-tiles at or above the
 // diagonal) and Y an n x k fp32 scratch matrix; not with nm_n or q_bits.
-// Layers whose sizes the aligned products do not take (n or k no multiple of 64):
-// the sweep then works on Wk (np x ldo) and EW (np rows) in the place of W_out and
-// the workspace's own, with rows padded to np and columns to ldo (multiples of 64);
-// L, D (U) and Y are given at that size, zero-padded.
-struct SweepPad {
-  float* Wk;
-  float* EW;
-  int64_t np, ldo;
-};
-int super_width(int B);  // columns of a super-block
 duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64_t ldw, const float* L,
                      int64_t ldl, const float* D, int64_t ldd, const float* fac, double p_w, const SweepOpts& o, int B,
                      const uint32_t* mask_in, float* W_out, void* W_out_lowp, uint32_t* mask_out,
                      float* scores_out, void* ws, void* pk, size_t pk_bytes, hipStream_t s,
-                     const float* U = nullptr, int64_t ldu = 0, float* Y = nullptr, const SweepPad* pad = nullptr);
+                     const float* U = nullptr, int64_t ldu = 0, float* Y = nullptr);
 
 }  // namespace duo

@@ -42,40 +42,56 @@ __global__ __launch_bounds__(256) void fac_kernel(float* Q, int64_t ldq, const f
   for (int i = t0 + threadIdx.x; i <= p; i += 256) Q[(int64_t)p * ldq + i] = 0.f;
 }
 
+struct ScoreWs {
+  float* Q;
+  size_t bytes;
+};
+
+ScoreWs carve(void* ws, int64_t k) {
+  Carver c(ws);
+  ScoreWs w;
+  w.Q = c.take<float>((size_t)k * k);
+  w.bytes = c.off;
+  return w;
+}
+
 }  // namespace
 
-size_t score_ws_bytes(int64_t k) { return align_up((size_t)k * k * sizeof(float)); }
+size_t score_ws_bytes(int64_t k) { return carve(nullptr, k).bytes; }
 size_t score_pk_bytes(int64_t k) { return split_bytes(k, k, k, 1); }
 
-duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k, int64_t kp,
-                     float* D, int64_t ldd, float* fac, float* Q, void* pk, size_t pk_bytes, hipStream_t s) {
+const float* score_u(const void* ws, int64_t k) { return carve(const_cast<void*>(ws), k).Q; }
+
+duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k, float* D,
+                     int64_t ldd, float* fac, void* ws, void* pk, size_t pk_bytes, hipStream_t s) {
+  const ScoreWs w = carve(ws, k);
   // Q = G L on upper tiles; L[l][i] = 0 for l < i, so l starts at the tile column
   GemmDesc q{};
-  q.M = (int)kp;
-  q.N = (int)kp;
-  q.C = Q;
-  q.ldc = kp;
+  q.M = (int)k;
+  q.N = (int)k;
+  q.C = w.Q;
+  q.ldc = k;
   q.beta = 0.f;
   q.tri = TRI_UPPER;
   q.order = ORDER_PLAIN;  // K range [j0, k): the first columns are the longest
   q.nterms = 1;
-  q.t[0] = GemmTerm{G, ldg, 1, L, ldl, 1, (int)kp, 1.f, KLO_COL, KHI_FULL};
+  q.t[0] = GemmTerm{G, ldg, 1, L, ldl, 1, (int)k, 1.f, KLO_COL, KHI_FULL};
   duo_status st = gemm_f32_split(q, pk, pk_bytes, s, ZERO_BELOW, ZERO_BELOW);  // G's upper triangle, L's lower
   if (st != DUO_OK) return st;
-  hipLaunchKernelGGL(fac_kernel, dim3((unsigned)k), dim3(256), 0, s, Q, kp, L, ldl, a, (int)k, fac);
+  hipLaunchKernelGGL(fac_kernel, dim3((unsigned)k), dim3(256), 0, s, w.Q, (int64_t)k, L, ldl, a, (int)k, fac);
   DUO_LAUNCH_CHECK();
-  if (!D) return DUO_OK;  // the Y form of the sweep reads U instead
+  if (!D) return DUO_OK;  // the Y form of the sweep reads U (score_u) instead
   // D = U L^T on upper tiles: D[p][j] = sum_{p < i <= j} U[p][i] L[j][i]
   GemmDesc d{};
-  d.M = (int)kp;
-  d.N = (int)kp;
+  d.M = (int)k;
+  d.N = (int)k;
   d.C = D;
   d.ldc = ldd;
   d.beta = 0.f;
   d.tri = TRI_UPPER;
   d.order = ORDER_DIAG;  // K range [i0, j0 + 128): grows with the distance from the diagonal
   d.nterms = 1;
-  d.t[0] = GemmTerm{Q, kp, 1, L, ldl, 0, (int)kp, 1.f, KLO_ROW, KHI_COL};
+  d.t[0] = GemmTerm{w.Q, k, 1, L, ldl, 0, (int)k, 1.f, KLO_ROW, KHI_COL};
   return gemm_f32_split(d, pk, pk_bytes, s, ZERO_UPTO);  // U is strictly upper
 }
 

@@ -24,8 +24,6 @@
 //            fp32 MFMA GEMM (W0 = the columns' values before pruning).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
 #include <utility>
 
 #include "internal.h"
@@ -197,8 +195,7 @@ __device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
 template <int HB>
 __global__ __launch_bounds__(256) void sel_hist_kernel(const float* __restrict__ W, int64_t ldw, int n, int Bb, int j0,
                                                        const float* __restrict__ fac, uint32_t* hist,
-                                                       float* scores_out, int64_t lds, int do_hist, SelState* st,
-                                                       int sh0) {
+                                                       float* scores_out, int do_hist, SelState* st, int sh0) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lh[];  // [kBins0]
   __shared__ uint32_t rng[8];
   const int tid = threadIdx.x;
@@ -249,7 +246,7 @@ __global__ __launch_bounds__(256) void sel_hist_kernel(const float* __restrict__
     __syncthreads();
     for_rows(Wc, ldw, r0, r1, rs, cv, [&](int r, float w) {
       const float S = weight_score(w, fc);
-      if (scores_out) scores_out[(int64_t)r * lds + j0 + c] = S;
+      if (scores_out) scores_out[(int64_t)r * ldw + j0 + c] = S;
       if (do_hist) {
         const uint32_t b = orderable(S) >> sh0;
         atomicAdd(&lh[b], 1u);
@@ -730,7 +727,7 @@ __global__ __launch_bounds__(256) void ib_image_kernel(const float* __restrict__
 // rows would otherwise need more than one workgroup per CU (the LDS image
 // allows one), so that a block finishes in one round over the CUs.
 template <bool NM, bool QUANT, bool YR, int ROWS>
-__global__ __launch_bounds__(ROWS * IB_Q) void inblock_kernel(float* __restrict__ Wo, int64_t ldo, int n, int k, int j0, int Bb, int64_t ew_ld,
+__global__ __launch_bounds__(ROWS * IB_Q) void inblock_kernel(float* __restrict__ Wo, int n, int k, int j0, int Bb, int64_t ew_ld,
                                                       const float* __restrict__ fac, const SelState* st, int mode,
                                                       const uint32_t* __restrict__ mask_in, float* __restrict__ EW,
                                                       uint8_t* __restrict__ bmask, IbOpts opt,
@@ -753,9 +750,9 @@ __global__ __launch_bounds__(ROWS * IB_Q) void inblock_kernel(float* __restrict_
   for (int i = 0; i < IB_I; ++i) {
     const int c = q + IB_Q * i;
     const bool cv = rv && c < Bb;
-    wv[i] = Wo[cv ? (int64_t)row * ldo + j0 + c : 0];
+    wv[i] = Wo[cv ? (int64_t)row * k + j0 + c : 0];
     fv[i] = fac[c < Bb ? j0 + c : j0];
-    if constexpr (YR) yv[i] = cv ? Yp[(int64_t)row * ldo + j0 + c] : 0.f;
+    if constexpr (YR) yv[i] = cv ? Yp[(int64_t)row * k + j0 + c] : 0.f;
   }
   if (tid < 256) {  // the image in 4 KB rows of 256 x 16 bytes
     const uint8_t* src = (const uint8_t*)img + (tid >> 6) * 1024 + (tid & 63) * 16;
@@ -811,7 +808,7 @@ __global__ __launch_bounds__(ROWS * IB_Q) void inblock_kernel(float* __restrict_
   for (int i = 0; i < IB_I; ++i) {
     const int c = q + IB_Q * i;
     if (rv && c < Bb) {
-      Wo[(int64_t)row * ldo + j0 + c] = s.w[i];
+      Wo[(int64_t)row * k + j0 + c] = s.w[i];
       EW[(int64_t)row * ew_ld + c] = YR ? (yv[i] + s.y[i]) - s.e[i] : s.e[i];
       EW[(int64_t)row * ew_ld + (ew_ld >> 1) + c] = s.w0[i];
       bmask[(int64_t)row * k + j0 + c] = (uint8_t)((s.kb[i] >> q) & 1u);
@@ -827,15 +824,15 @@ __global__ void zero_kernel(float* __restrict__ p, int64_t cnt) {
   for (int64_t i = cnt / 4 * 4 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += stride) p[i] = 0.f;
 }
 
-__global__ void init_w_kernel(const void* W, int dtype, int64_t ldw, int n, int k, float* Wo, int64_t ldo) {
+__global__ void init_w_kernel(const void* W, int dtype, int64_t ldw, int n, int k, float* Wo) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= (int64_t)n * k) return;
   const int64_t r = id / k, c = id % k;
-  Wo[r * ldo + c] = dtype == DUO_BF16 ? bf16_bits_to_f32(((const uint16_t*)W)[r * ldw + c]) : ((const float*)W)[r * ldw + c];
+  Wo[id] = dtype == DUO_BF16 ? bf16_bits_to_f32(((const uint16_t*)W)[r * ldw + c]) : ((const float*)W)[r * ldw + c];
 }
 
-__global__ void finalize_kernel(const float* Wo, int64_t ldo, const uint8_t* bmask, int n, int k, int dtype, void* lowp,
-                                uint32_t* mask_out, float* Wout) {
+__global__ void finalize_kernel(const float* Wo, const uint8_t* bmask, int n, int k, int dtype, void* lowp,
+                                uint32_t* mask_out) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int words = (k + 31) / 32;
   if (mask_out && id < (int64_t)n * words) {
@@ -847,15 +844,11 @@ __global__ void finalize_kernel(const float* Wo, int64_t ldo, const uint8_t* bma
     }
     mask_out[id] = bits;
   }
-  if ((lowp || Wout) && id < (int64_t)n * k) {
-    const float v = Wo[id / k * ldo + id % k];
-    if (Wout) Wout[id] = v;
-    if (lowp) {
-      if (dtype == DUO_BF16)
-        ((uint16_t*)lowp)[id] = f32_to_bf16_bits(v);
-      else
-        ((float*)lowp)[id] = v;
-    }
+  if (lowp && id < (int64_t)n * k) {
+    if (dtype == DUO_BF16)
+      ((uint16_t*)lowp)[id] = f32_to_bf16_bits(Wo[id]);
+    else
+      ((float*)lowp)[id] = Wo[id];
   }
 }
 
@@ -929,11 +922,7 @@ __global__ void finalize4_kernel(const float* Wo, const uint8_t* bmask, int n, i
 // more there and lost at k = 4096 and 11008)
 constexpr int kSuper = 1024;
 
-}  // namespace
-
 int super_width(int B) { return B * (kSuper / B > 1 ? kSuper / B : 1); }
-
-namespace {
 
 struct SweepWs {
   SelState* st;
@@ -966,12 +955,8 @@ size_t sweep_pk_bytes(int64_t n, int64_t k, int B) { return split_bytes(n, k, su
 duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64_t ldw, const float* L, int64_t ldl,
                      const float* D, int64_t ldd, const float* fac, double p_w, const SweepOpts& o, int B,
                      const uint32_t* mask_in, float* W_out, void* W_out_lowp, uint32_t* mask_out, float* scores_out,
-                     void* ws, void* pk, size_t pk_bytes, hipStream_t s, const float* U, int64_t ldu, float* Y, const SweepPad* pad) {
+                     void* ws, void* pk, size_t pk_bytes, hipStream_t s, const float* U, int64_t ldu, float* Y) {
   const SweepWs w = carve(ws, n, k, B);
-  // the working matrix (np rows, ldo columns: n and k, or padded) and the errors
-  float* const Wk = pad ? pad->Wk : W_out;
-  float* const EW = pad ? pad->EW : w.EW;
-  const int64_t np = pad ? pad->np : n, ldo = pad ? pad->ldo : k;
   const bool yr = U != nullptr;  // Y form
   // the Y form with quantisation: only grids fixed at a block's first column,
   // where W[:, blk] holds the values of Algorithm 1 after the start product
@@ -979,14 +964,14 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
   const int64_t nk = n * k;
   const int64_t S = super_width(B);
   auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  const bool v4 = !pad && k % 32 == 0 && ldw % 4 == 0 && (reinterpret_cast<uintptr_t>(W) & 7) == 0 && al16(W_out) &&
+  const bool v4 = k % 32 == 0 && ldw % 4 == 0 && (reinterpret_cast<uintptr_t>(W) & 7) == 0 && al16(W_out) &&
                   (!W_out_lowp || al16(W_out_lowp)) && al16(ws);
   if (v4)
     hipLaunchKernelGGL(init_w4_kernel, dim3((unsigned)cdiv(nk / 4, 256)), dim3(256), 0, s, W, (int)w_dtype, ldw,
                        (int)n, (int)k, W_out);
   else
     hipLaunchKernelGGL(init_w_kernel, dim3((unsigned)cdiv(nk, 256)), dim3(256), 0, s, W, (int)w_dtype, ldw, (int)n,
-                       (int)k, Wk, ldo);
+                       (int)k, W_out);
   DUO_LAUNCH_CHECK();
   hipLaunchKernelGGL(sel_reset_kernel, dim3(1), dim3(256), 0, s, w.st, w.hist);
   DUO_LAUNCH_CHECK();
@@ -995,9 +980,8 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
                      yr ? ldu : ldd, (int)k, B, w.img);
   DUO_LAUNCH_CHECK();
   if (yr) {
-    const int64_t ny = np * ldo;
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)(cdiv(ny, 1024) < 8192 ? cdiv(ny, 1024) : 8192)), dim3(256), 0, s,
-                       Y, ny);
+    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)(cdiv(nk, 1024) < 8192 ? cdiv(nk, 1024) : 8192)), dim3(256), 0, s,
+                       Y, nk);
     DUO_LAUNCH_CHECK();
   }
   const bool nm = o.nm_n > 0 && !mask_in;
@@ -1051,15 +1035,14 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
       // Y form: W[:, blk] += Y[:, blk] L[blk, blk]^T (the residual terms of the
       // block's own columns owed by the earlier blocks)
       GemmDesc c{};
-      const int Bp = (int)std::min<int64_t>(B, ldo - j0);  // padded: Y and L are zero past k
-      c.M = (int)np;
-      c.N = Bp;
-      c.C = Wk + j0;
-      c.ldc = ldo;
+      c.M = (int)n;
+      c.N = Bb;
+      c.C = W_out + j0;
+      c.ldc = k;
       c.beta = 1.f;
       c.tri = TRI_ALL;
       c.nterms = 1;
-      c.t[0] = GemmTerm{Y + j0, ldo, 1, L + j0 * ldl + j0, ldl, 0, Bp, 1.f, KLO_ZERO, KHI_FULL};
+      c.t[0] = GemmTerm{Y + j0, k, 1, L + j0 * ldl + j0, ldl, 0, Bb, 1.f, KLO_ZERO, KHI_FULL};
       prof_begin(DUO_PROF_TRAIL, s);
       duo_status st = gemm_f32(c, s);
       prof_end(DUO_PROF_TRAIL, s);
@@ -1068,24 +1051,24 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
     prof_begin(DUO_PROF_SELECT, s);
     if (mode == MODE_SELECT || (scores_out && mode != MODE_NM)) {
       hipLaunchKernelGGL(scores_out ? sel_hist_kernel<0> : hist_k, dim3(P), dim3(256), hist_lds, s,
-                         (const float*)Wk, ldo, (int)n, Bb, (int)j0, fac, w.hist, scores_out, k,
+                         (const float*)W_out, k, (int)n, Bb, (int)j0, fac, w.hist, scores_out,
                          mode == MODE_SELECT ? 1 : 0, w.st, sh0);
       DUO_LAUNCH_CHECK();
     }
     if (mode == MODE_SELECT) {
-      hipLaunchKernelGGL(gather_k, dim3(P), dim3(256), 0, s, (const float*)Wk, ldo, (int)n, Bb, (int)j0, fac,
+      hipLaunchKernelGGL(gather_k, dim3(P), dim3(256), 0, s, (const float*)W_out, k, (int)n, Bb, (int)j0, fac,
                          (uint32_t)z, idx_bits, (const uint32_t*)w.hist, w.st, w.cand, sh0);
       DUO_LAUNCH_CHECK();
-      hipLaunchKernelGGL(resolve_k, dim3(1), dim3(256), sel_lds, s, (const float*)Wk, ldo, (int)n, Bb,
+      hipLaunchKernelGGL(resolve_k, dim3(1), dim3(256), sel_lds, s, (const float*)W_out, k, (int)n, Bb,
                          (int)j0, fac, (uint32_t)z, idx_bits, w.hist, w.st, (const unsigned long long*)w.cand, sh0);
       DUO_LAUNCH_CHECK();
     }
     prof_end(DUO_PROF_SELECT, s);
     prof_begin(DUO_PROF_INBLOCK, s);
     const int64_t sb0 = j0 / S * S, sb1 = sb0 + S < k ? sb0 + S : k;
-    hipLaunchKernelGGL(ib_kern, dim3((unsigned)cdiv(n, ib_rows)), dim3(ib_rows * IB_Q), ib_lds, s, Wk, ldo, (int)n, (int)k,
+    hipLaunchKernelGGL(ib_kern, dim3((unsigned)cdiv(n, ib_rows)), dim3(ib_rows * IB_Q), ib_lds, s, W_out, (int)n, (int)k,
                        (int)j0, Bb, (int64_t)2 * S, fac, (const SelState*)w.st, mode, mask_in,
-                       EW + (j0 - sb0), w.bmask, ibo, scores_out, (const float*)(w.img + (j0 / B) * IB_IMG),
+                       w.EW + (j0 - sb0), w.bmask, ibo, scores_out, (const float*)(w.img + (j0 / B) * IB_IMG),
                        (const float*)Y);
     DUO_LAUNCH_CHECK();
     prof_end(DUO_PROF_INBLOCK, s);
@@ -1095,10 +1078,10 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
     if (c0 < c1) {
       const int K = (int)(j1 - u0);
       GemmDesc g{};
-      g.M = (int)np;
-      g.N = (int)((c1 == k ? ldo : c1) - c0);  // padded: whole tiles
-      g.C = Wk + c0;
-      g.ldc = ldo;
+      g.M = (int)n;
+      g.N = (int)(c1 - c0);
+      g.C = W_out + c0;
+      g.ldc = k;
       g.beta = 1.f;
       g.tri = TRI_ALL;
       g.nterms = 2;
@@ -1107,15 +1090,15 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
         // independent, one launch
         g.dual = 1;
         g.C2 = Y + c0;
-        g.t[0] = GemmTerm{EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, 1.f, KLO_ZERO, KHI_FULL};
-        g.t[1] = GemmTerm{EW + S + (u0 - sb0), 2 * S, 1, U + u0 * ldu + c0, ldu, 1, K, 1.f, KLO_ZERO, KHI_FULL};
+        g.t[0] = GemmTerm{w.EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, 1.f, KLO_ZERO, KHI_FULL};
+        g.t[1] = GemmTerm{w.EW + S + (u0 - sb0), 2 * S, 1, U + u0 * ldu + c0, ldu, 1, K, 1.f, KLO_ZERO, KHI_FULL};
         prof_begin(DUO_PROF_TRAIL, s);
         duo_status st = gemm_f32_split(g, pk, pk_bytes, s);
         prof_end(DUO_PROF_TRAIL, s);
         if (st != DUO_OK) return st;
       } else {
-        g.t[0] = GemmTerm{EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, -1.f, KLO_ZERO, KHI_FULL};
-        g.t[1] = GemmTerm{EW + S + (u0 - sb0), 2 * S, 1, D + u0 * ldd + c0, ldd, 1, K, 1.f, KLO_ZERO, KHI_FULL};
+        g.t[0] = GemmTerm{w.EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, -1.f, KLO_ZERO, KHI_FULL};
+        g.t[1] = GemmTerm{w.EW + S + (u0 - sb0), 2 * S, 1, D + u0 * ldd + c0, ldd, 1, K, 1.f, KLO_ZERO, KHI_FULL};
         prof_begin(DUO_PROF_TRAIL, s);
         duo_status st = gemm_f32(g, s);
         prof_end(DUO_PROF_TRAIL, s);
@@ -1123,7 +1106,7 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
       }
     }
   }
-  if (mask_out || W_out_lowp || pad) {
+  if (mask_out || W_out_lowp) {
     const int64_t words = cdiv(k, 32);
     if (v4) {
       const int64_t cnt = nk / 4 > n * words ? nk / 4 : n * words;
@@ -1131,9 +1114,8 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
                          (const uint8_t*)w.bmask, (int)n, (int)k, (int)w_dtype, W_out_lowp, mask_out);
     } else {
       const int64_t cnt = nk > n * words ? nk : n * words;
-      hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)cdiv(cnt, 256)), dim3(256), 0, s, (const float*)Wk, ldo,
-                         (const uint8_t*)w.bmask, (int)n, (int)k, (int)w_dtype, W_out_lowp, mask_out,
-                         pad ? W_out : nullptr);
+      hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)cdiv(cnt, 256)), dim3(256), 0, s, (const float*)W_out,
+                         (const uint8_t*)w.bmask, (int)n, (int)k, (int)w_dtype, W_out_lowp, mask_out);
     }
     DUO_LAUNCH_CHECK();
   }
