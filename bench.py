@@ -23,8 +23,8 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_FP32_TFLOPS = 157.3    # MI355X dense fp32 MFMA
 # Large fp32 products run as six bf16 products of exactly split operands: from this
-# k up most of the factorisation, score and lazy-update flop do, and their rates are
-# priced against a sixth of the bf16 peak
+# k up most of the score and lazy-update flop do (not the factorisation's, nor a
+# quantised layer's), and their rates are priced against a sixth of the bf16 peak
 SPLIT_MIN_K = 7168
 PEAK_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
@@ -493,7 +493,9 @@ def main():
     # inverse, Cholesky, full products) and is printed beside it
     chol_score_flop = (3 if yform else 4) * k ** 3 / 3
     chol_score_flop_plain = 8 * k ** 3 / 3
-    f32_peak = PEAK_SPLIT_TFLOPS if k >= SPLIT_MIN_K else PEAK_FP32_TFLOPS
+    f32_peak = PEAK_SPLIT_TFLOPS if k >= SPLIT_MIN_K and not args.quant else PEAK_FP32_TFLOPS
+    # the factorisation's two thirds of k^3 at the fp32 peak, the score terms' rest at theirs
+    chol_score_peak = chol_score_flop / (2 * k ** 3 / 3 / PEAK_FP32_TFLOPS + (chol_score_flop - 2 * k ** 3 / 3) / f32_peak)
     # the Gram kernel multiplies in the calibration input's precision: bf16
     # MFMA for bf16 inputs, fp32 MFMA for fp32 inputs
     gram_peak = PEAK_BF16_TFLOPS if c["x_dtype"] == torch.bfloat16 else PEAK_FP32_TFLOPS
@@ -526,7 +528,7 @@ def main():
         "trailing_tflops": trail_tflops,
         "trailing_frac": trail_tflops / f32_peak,
         "chol_score_tflops": chol_score_flop / ((per_step("chol") + per_step("score")) * 1e-3) / 1e12,
-        "chol_score_frac": chol_score_flop / ((per_step("chol") + per_step("score")) * 1e-3) / 1e12 / f32_peak,
+        "chol_score_frac": chol_score_flop / ((per_step("chol") + per_step("score")) * 1e-3) / 1e12 / chol_score_peak,
         "fp32_product_peak_TFLOPs": f32_peak,
         "chol_score_flop_count": ("k^3 (implemented route, Y form: no D)" if yform else "(4/3) k^3 (implemented route)")
                                  + "; plain route (8/3) k^3 gives "

@@ -213,13 +213,13 @@ duo_status duo_chol_inv(float* H_inout, int64_t k, int64_t ldh, double damp_rati
                         size_t ws_bytes, void* stream) {
   if (!H_inout || ldh < k || !std::isfinite(damp_ratio) || damp_ratio < 0.0) return DUO_ERR_INVALID_ARG;
   if (!k_ok(k)) return k < 1 ? DUO_ERR_INVALID_ARG : DUO_ERR_UNSUPPORTED;
-  if (!ws_ok(ws, ws_bytes, chol_ws_bytes(k, false))) return DUO_ERR_WORKSPACE;
+  if (!ws_ok(ws, ws_bytes, chol_ws_bytes(k))) return DUO_ERR_WORKSPACE;
   duo_status d = device_ok();
   if (d != DUO_OK) return d;
   CholStatus* st = nullptr;
   const hipStream_t s = (hipStream_t)stream;
   prof_begin(DUO_PROF_CHOL, s);
-  duo_status r = chol_run(H_inout, k, ldh, damp_ratio, ws, ws_bytes, s, &st);
+  duo_status r = chol_run(H_inout, k, ldh, damp_ratio, ws, s, &st);
   prof_end(DUO_PROF_CHOL, s);
   if (r != DUO_OK) return r;
   if (!info) return DUO_OK;
@@ -314,7 +314,9 @@ duo_status duo_prune_layer(const void* W, int32_t w_dtype, int64_t n, int64_t k,
   // n = k = 4096: 0.17 ms slower per layer; k = 11008: 2 ms faster).
   const bool yform = o.form == DUO_FORM_Y || (o.form == DUO_FORM_AUTO && y_ok && k >= kYFormMinK);
   void* const pk = (uint8_t*)ws + pw.bytes;
-  const size_t pk_bytes = ws_bytes - pw.bytes;
+  // A quantised value may round to the next code when a last bit of what it is
+  // computed from differs; quantised layers keep the fp32 instructions.
+  const size_t pk_bytes = o.q_bits ? 0 : ws_bytes - pw.bytes;
   prof_begin(DUO_PROF_SCORE, s);
   duo_status r = score_run(L, ldl, G, ldg, a, k, yform ? nullptr : w.D, k, w.fac, w.score, pk, pk_bytes, s);
   prof_end(DUO_PROF_SCORE, s);

@@ -18,7 +18,6 @@
 //   4. L = N^T written to the lower triangle; the strict upper set to zero.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <utility>
 
 #include "internal.h"
@@ -370,7 +369,7 @@ CholWs carve(void* ws, int64_t k) {
 // All complete nodes of a level share one batched launch per product; a node
 // containing the ragged last block gets its own.
 duo_status merge_nodes(float* H, int64_t ldh, int64_t k, int64_t span, int64_t half, int64_t q0, int nodes,
-                       float* X, void* pk, size_t pk_bytes, hipStream_t s) {
+                       float* X, hipStream_t s) {
   const int64_t r_lo = q0 * span * kTile, r_mid = r_lo + half * kTile;
   const int64_t r_hi = r_lo + span * kTile < k ? r_lo + span * kTile : k;
   const int m1 = (int)(r_mid - r_lo), m2 = (int)(r_hi - r_mid);
@@ -390,7 +389,7 @@ duo_status merge_nodes(float* H, int64_t ldh, int64_t k, int64_t span, int64_t h
   a.sC = (int64_t)m1 * m2;
   a.sA[0] = diag_step;
   a.sB[0] = diag_step;
-  duo_status st = gemm_f32_split(a, pk, pk_bytes, s, ZERO_NONE, ZERO_ABOVE);
+  duo_status st = gemm_f32(a, s);
   if (st != DUO_OK) return st;
   // V12 <- -N11 X (N11 upper: for output row tile i only l >= i-tile start)
   GemmDesc b{};
@@ -407,19 +406,19 @@ duo_status merge_nodes(float* H, int64_t ldh, int64_t k, int64_t span, int64_t h
   b.sC = diag_step;
   b.sA[0] = diag_step;
   b.sB[0] = (int64_t)m1 * m2;
-  return gemm_f32_split(b, pk, pk_bytes, s, ZERO_BELOW);
+  return gemm_f32(b, s);
 }
 
-duo_status trinv(float* H, int64_t ldh, int64_t k, int T, float* X, void* pk, size_t pk_bytes, hipStream_t s) {
+duo_status trinv(float* H, int64_t ldh, int64_t k, int T, float* X, hipStream_t s) {
   for (int64_t half = 1; half < T; half *= 2) {
     const int64_t span = 2 * half;
     const int64_t full = k / (span * kTile);  // nodes with both halves complete (no ragged block)
     if (full > 0) {
-      duo_status st = merge_nodes(H, ldh, k, span, half, 0, (int)full, X, pk, pk_bytes, s);
+      duo_status st = merge_nodes(H, ldh, k, span, half, 0, (int)full, X, s);
       if (st != DUO_OK) return st;
     }
     if (full * span + half < T) {  // the node holding the tail
-      duo_status st = merge_nodes(H, ldh, k, span, half, full, 1, X, pk, pk_bytes, s);
+      duo_status st = merge_nodes(H, ldh, k, span, half, full, 1, X, s);
       if (st != DUO_OK) return st;
     }
   }
@@ -428,32 +427,12 @@ duo_status trinv(float* H, int64_t ldh, int64_t k, int T, float* X, void* pk, si
 
 }  // namespace
 
-// blocks per group of the factorisation (chol_run)
-static int chol_group(int64_t T) { return T >= 64 ? 8 : 4; }
-
-// Packed operands of the split products: the trailing updates (both operands are
-// one panel) and the merges of every level of the inverse.
-static size_t chol_pk_bytes(int64_t k) {
-  const int64_t T = cdiv(k, kTile);
-  size_t b = split_bytes(k, 0, chol_group(T) * kTile, 1);
-  for (int64_t half = 1; half < T; half *= 2) {
-    const int64_t span = 2 * half, full = k / (span * kTile), m = half * kTile;
-    if (full > 0) b = std::max(b, split_bytes(m, m, m, full));
-    const int64_t m2 = k - full * span * kTile - m;  // the tail node's second half
-    if (m2 > 0) b = std::max({b, split_bytes(m, m2, m2, 1), split_bytes(m, m2, m, 1)});
-  }
-  return b;
-}
-
-size_t chol_ws_bytes(int64_t k, bool full) { return carve(nullptr, k).bytes + (full ? chol_pk_bytes(k) : 0); }
+size_t chol_ws_bytes(int64_t k) { return carve(nullptr, k).bytes; }
 
 constexpr size_t kDiagLds = (size_t)(2 * kTile * DS + 4) * sizeof(float);
 
-duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, size_t ws_bytes, hipStream_t s,
-                    CholStatus** status_dev) {
+duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, hipStream_t s, CholStatus** status_dev) {
   const CholWs w = carve(ws, k);
-  void* const pk = (uint8_t*)ws + w.bytes;
-  const size_t pk_bytes = ws_bytes - w.bytes;
   if (duo_status d = set_max_lds((const void*)diag_factor_kernel, kDiagLds); d != DUO_OK) return d;
   *status_dev = w.st;
   const int T = (int)cdiv(k, kTile);
@@ -485,9 +464,9 @@ duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, siz
   // the leading matrix takes all of the group's updates in one product with
   // K = 128 kGroup.  Every column still receives every update before its own
   // block is factored; only the fp32 summation order changes.
-  // (8 blocks per group from 64 blocks up: at k = 11008 12.1 -> 12.0 ms, at k = 6144 4.2
-  // -> 4.3, where the longer strips cost more than the fewer updates save)
-  const int kGroup = chol_group(T);
+  // (8 blocks per group from 128 blocks up: measured 170 -> 159 ms at
+  // k = 28672, while at k = 4096 the longer strips cost more than they save)
+  const int kGroup = T >= 128 ? 8 : 4;
   for (int top = T - 1; top >= 0;) {
     const int lo = top - kGroup + 1 > 0 ? top - kGroup + 1 : 0;
     const int64_t top_end = (int64_t)top * kTile + kTile <= k ? (int64_t)top * kTile + kTile : k;
@@ -525,7 +504,7 @@ duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, siz
     u.tri = TRI_UPPER;
     u.nterms = 1;
     u.t[0] = GemmTerm{H + r, ldh, 1, H + r, ldh, 0, (int)(top_end - r), -1.f, KLO_ZERO, KHI_FULL};
-    duo_status st = gemm_f32_split(u, pk, pk_bytes, s);
+    duo_status st = gemm_f32(u, s);
     if (st != DUO_OK) return st;
     top = lo - 1;
   }
@@ -533,7 +512,7 @@ duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, siz
   hipLaunchKernelGGL(place_diag_kernel, dim3(T, kTile / 16), dim3(256), 0, s, H, ldh, (int)k, (const float*)w.vinv,
                      pvec);
   DUO_LAUNCH_CHECK();
-  duo_status st = trinv(H, ldh, k, T, w.X, pk, pk_bytes, s);
+  duo_status st = trinv(H, ldh, k, T, w.X, s);
   if (st != DUO_OK) return st;
   const int T64 = (int)cdiv(k, 64);
   hipLaunchKernelGGL(transpose_upper_kernel, dim3(T64 * (T64 + 1) / 2), dim3(256), 0, s, H, ldh, (int)k);

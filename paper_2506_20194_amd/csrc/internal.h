@@ -96,7 +96,7 @@ duo_status gemm_f32(const GemmDesc& d, hipStream_t s);
 // zero_a, zero_b: entries of a one-term product's operands that count as zero
 // whatever is stored there (the tiles are 256 wide, and inside a 256-wide diagonal
 // tile the 128-wide block below (above) the diagonal need not hold zeros).
-enum { ZERO_NONE = 0, ZERO_BELOW = 1, ZERO_UPTO = 2, ZERO_ABOVE = 3 };  // l < r, l <= r, l > r (r: i of A, j of B)
+enum { ZERO_NONE = 0, ZERO_BELOW = 1, ZERO_UPTO = 2 };  // l < r, l <= r (r: i of A, j of B)
 size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products);
 duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s, int zero_a = ZERO_NONE,
                           int zero_b = ZERO_NONE);
@@ -108,9 +108,8 @@ struct CholStatus {
   int status;
   int pad;
 };
-// full = false: without the packed operands of the split products
-size_t chol_ws_bytes(int64_t k, bool full = true);
-duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, size_t ws_bytes, hipStream_t s,
+size_t chol_ws_bytes(int64_t k);
+duo_status chol_run(float* H, int64_t k, int64_t ldh, double damp, void* ws, hipStream_t s,
                     CholStatus** status_dev);
 
 // ---- stage 3 (score.hip, sweep.hip) ----

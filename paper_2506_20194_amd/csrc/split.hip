@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs A) {
   // the contraction indices of row r that do not count as zero (a chain of
   // conditions per entry in the place of these bounds was miscompiled by ROCm 7.2)
   const int lo = A.zero == ZERO_BELOW ? r : A.zero == ZERO_UPTO ? r + 1 : 0;
-  const int hi = r >= A.rows ? 0 : A.zero == ZERO_ABOVE ? min(r + 1, A.K) : A.K;
+  const int hi = r >= A.rows ? 0 : A.K;
   for (int q = 0; q < KPB; ++q) {
     const int kb = blockIdx.y * KPB + q;
     if (kb >= A.nkb) break;

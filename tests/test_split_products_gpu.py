@@ -1,5 +1,5 @@
 """The fp32 products that run as six bf16 products of exactly split operands:
-score terms, inverse factor and Y-form sweep at sizes where they take that path,
+score terms and Y-form sweep at sizes where they take that path,
 k a multiple of 256, of 8 and of nothing, with NaN wherever an operand is not to
 be read, and with workspaces that leave the packed operands no room (the fp32
 instructions then do the work).  Bars: relative Frobenius error 16 sqrt(k) 2^-24
@@ -52,28 +52,6 @@ def test_score_terms(duo_lib, k):
         D, f = duo_lib.duo_score_terms(L, bad, a, D=D, ws=ws)
         assert _rel(D.triu(1), R.triu(1)) < _bar(k)
         assert _rel(f, fac) < _bar(k)
-
-
-@pytest.mark.parametrize("k", KS)
-def test_chol_inv(duo_lib, k):
-    print("[case] split inverse factor", k, flush=True)
-    g = torch.Generator(device="cuda").manual_seed(k)
-    X = torch.randn((2 * k, k), generator=g, device="cuda")
-    H = X.t() @ X
-    size = duo_lib.duo_workspace_size(duo_lib.DUO_OP_CHOL_INV, 0, k, 0, 0)
-    Hd = H.double().triu()
-    Hd = Hd + Hd.triu(1).t()
-    Hd.diagonal().add_(0.01 * Hd.diagonal().mean())
-    probe = torch.randn((k, 8), generator=g, device="cuda", dtype=torch.float64)
-    for nbytes in (size, size - 4096, (size - size // 3) // 256 * 256):
-        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-        L = H.clone()
-        duo_lib.duo_chol_inv(L, 0.01, ws=ws)
-        Ld = L.double()
-        assert torch.equal(Ld, Ld.tril())
-        # L^T (H + lambda I) L = I on random vectors
-        r = Ld.t() @ (Hd @ (Ld @ probe))
-        assert float((r - probe).norm() / probe.norm()) < 4 * _bar(k)
 
 
 @pytest.mark.parametrize("n,k", [(4096, 8192), (4100, 8200), (4099, 8195)])
