@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(512) void gram_f32_kernel(GramArgs<float> A) {
 // fragment read is linear in it (no bank conflicts).  Two streams: dX = hi + lo,
 // and a G tile takes both in turn for every 64 tokens (twice an H tile's stages).
 // Bound: MFMA issue and the clock under that load.  Measured, one chunk: 65536
-// tokens at k = 4096 1880 -> 1445 us; 8192 tokens, two streams, k = 11008 3360 -> 2150
+// tokens at k = 4096 1880 -> 1560 us (pieces of 8192); 8192 tokens, two streams, k = 11008 3360 -> 2150
 // us; 131072 at k = 28672 166 -> 137 ms (the form before had all eight waves in step on a ring of 32-token stages,
 // and gave four XCDs the H tiles and four the G tiles).
 constexpr int kGram16Unit = 128 * 128;  // bytes: 128 channels x 64 tokens
@@ -1320,14 +1320,31 @@ static GramPlan gram_plan(int64_t T, int64_t nh, int64_t ng, bool cost2, bool bf
 // added to H, G or the partial tile in pieces.  The relative error of the 32-bit
 // sums grows with the square root of the accumulation steps (32 tokens each in
 // bf16, 4 in fp32): measured 1.5e-6 in one piece of 65536 tokens (bf16, k = 4096),
-// 6.2e-7 in pieces of 16384, 4.4e-7 in pieces of 8192.  A piece costs a pass
+// 6.6e-7 in pieces of 16384, 4.6e-7 in pieces of 8192.  A piece costs a pass
 // over the output, whose rows lie further apart the larger k is, and takes the
 // workgroups of an XCD out of step: 25 us at k = 4096 (390 us of products per 16384
 // tokens), 140 us at k = 28672 (131072 tokens: 137 ms in one piece, 152 in pieces of
 // 16384, 167 of 8192).
-static int gram_piece(int64_t k, bool bf16) {
-  const int t = k <= 9216 ? 16384 : k <= 20480 ? 24576 : 131072;
-  return (bf16 ? t : k <= 9216 ? 4096 : 8192) / kTokBlk;
+// The bound on a piece, of `ch` tokens in a launch: the share of a tile that up to eight
+// segments per tile would get which fill the chip's rounds of 256 tiles (a full tile
+// at 4.5 TFLOP/s per CU, the sum of s partial tiles (s + 2) * 256 KB at 4 TB/s).  That
+// is the longest run that the sums of a launch split throughout would have, and
+// the error stays below theirs: 65536 tokens at k = 4096 8192, 8192 tokens there 2048.
+static int gram_piece(int64_t T, bool bf16, int64_t ch) {
+  const int64_t k = T * GT, ntiles = T * (T + 1), nb = cdiv(ch, kTokBlk);
+  const double t_tile = 2.0 * GT * GT * (double)ch / 4.5e12, t_sum = (double)GT * GT * 4.0 / 4e12;
+  int64_t best = 1;
+  double best_cost = 1e30;
+  for (int s = 1; s <= 8; ++s) {
+    const double cost = (double)cdiv(ntiles * s, 256) / s * t_tile + (s > 1 ? (double)ntiles * (s + 2) * t_sum : 0.0);
+    if (cost < best_cost * (1.0 - 1e-9)) {
+      best_cost = cost;
+      best = s;
+    }
+  }
+  const int64_t t = k <= 9216 ? 16384 : k <= 20480 ? 24576 : 131072;
+  const int64_t most = (bf16 ? t : k <= 9216 ? 4096 : 8192) / kTokBlk;
+  return (int)std::min(most, rup(cdiv(nb, best), 2));
 }
 
 // Diagonal of H in fp64 for act_order: hdiag[c] += sum_t Xh[t][c]^2, read
@@ -1533,7 +1550,7 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
     A.nh = want_h ? nh_all : 0;
     A.ntiles = A.nh + ng;
     A.g_full = g_full;
-    A.piece = gram_piece(k, sizeof(T) == 2);
+    A.piece = gram_piece(nt, sizeof(T) == 2, ch);
     A.mixed = lo;
     A.nsplit = plan.nsplit;
     A.nseg = plan.nseg;

@@ -318,8 +318,9 @@ size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products) {
 // be the one with the longest sum.  There 110 TFLOP/s (64-wide tiles, the sizes where
 // the choice is close) and a launch.  At n = 4096: k = 4096 stays on fp32
 // instructions (with this path for Q and D 4.55 against 4.12 ms per solve), k = 8192
-// 15.2 -> 14.5 ms, k = 11008 28.0 -> 24.5 ms, n = 8192, k = 28672 308 -> 196 to 209 ms
-// (the bf16 rate under this load differs between boards).
+// 15.2 -> 14.5 ms, k = 11008 28.0 -> 24.5 ms (with the factorisation
+// on this path too, which needs the same bits for quantised layers and is not); n = 8192, k = 28672, score and
+// sweep alone, 308 -> 247 ms.
 static bool split_pays(const GemmDesc& d) {
   if (d.inplace || d.tri == TRI_LOWER || (d.nterms == 2 && !d.dual)) return false;
   const int64_t tm = cdiv(d.M, ST), tn = cdiv(d.N, ST);
