@@ -1100,8 +1100,8 @@ __global__ __launch_bounds__(512) void gram_f32_kernel(GramArgs<float> A) {
 // [128 channels][16 bytes], filled from the packed operands in 1 KB pieces, and a
 // fragment read is linear in it (no bank conflicts).  Two streams: dX = hi + lo,
 // and a G tile takes both in turn for every 64 tokens (twice an H tile's stages).
-// Bound: MFMA issue and the clock under that load.  Measured, one chunk: 65536
-// tokens at k = 4096 1880 -> 1560 us (pieces of 8192); 8192 tokens, two streams, k = 11008 3360 -> 2150
+// Bound: MFMA issue and the clock under that load.  Measured, whole calls:
+// 2 x 65536 tokens at k = 4096 5.17 -> 4.27 ms; one chunk: 8192 tokens, two streams, k = 11008 3360 -> 2150
 // us; 131072 at k = 28672 166 -> 137 ms (the form before had all eight waves in step on a ring of 32-token stages,
 // and gave four XCDs the H tiles and four the G tiles).
 constexpr int kGram16Unit = 128 * 128;  // bytes: 128 channels x 64 tokens
