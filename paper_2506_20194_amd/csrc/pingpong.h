@@ -16,8 +16,12 @@
 // p - 6, and every wave waits for its own part of it at the end of the memory
 // part of phase p - 1, before a barrier that all waves pass before any of them
 // enters phase p: at most the five units issued since may then be in flight.
-// Overwriting: a unit last read in phase p has been read by every wave when the
-// first of them enters phase p + 2, which is when its successor is issued.
+// Overwriting: a unit is overwritten (its successor issued) two phases after the
+// one that last reads it, and by then every wave's reads of it have returned:
+// waves 4-7 pass the barrier that lets waves 0-3 into phase p + 2 at the end of
+// their memory part of phase p + 1.  The fragments that are used in the phase that
+// reads them have been waited for by then.  B0 is read a phase before its first
+// use (in phase 3 of the stage before), so phase 0's memory part waits for it.
 #pragma once
 
 #include "common.h"
@@ -51,6 +55,18 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// Wait until at most N of this wave's LDS reads are in flight (they return in
+// order).  No LDS read moves across it.
+template <int N>
+__device__ __forceinline__ void wait_lds() {
+  static_assert(N >= 0 && N < 16, "lgkmcnt range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (N << 8));
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
 }
 
 // Barrier between the parts of a phase: nothing moves across it, and nothing
@@ -112,6 +128,7 @@ __device__ __forceinline__ void pp_loop(int nst, f4 (&acc)[2 * HA][4], const Iss
   auto stage = [&](int t, int par, const u32x4 (&x0)[2][2], u32x4 (&nx)[2][2]) {
     read_a(par, 0, fa);
     issue(1, t + 1, par ^ 1);
+    wait_lds<2 * HA>();  // all but read_a's: B0 of this stage, whose successor the next phase issues
     mem_end(0);
     mma(0, 0, fa, x0);
     read_b(par, 1, fb1);
