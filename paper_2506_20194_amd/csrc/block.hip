@@ -505,8 +505,10 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* _
     }
   };
 
-  // pass 1: maximum m and sum l of exp over this half's keys of query qw + l32
-  float m = -INFINITY, l = 0.f;
+  // pass 1: maximum m and sum l of exp over this half's keys of query qw + l32.
+  // mc = m cexp as rounded: every exponential is relative to that number, also
+  // where a sum moves to a new maximum, so its rounding drops out of p
+  float m = -INFINITY, mc = -INFINITY, l = 0.f;
   issue(Kx, 0, sm[0][0], false);
   issue(Kx, 1, sm[0][1], false);
   int kb = 0;
@@ -528,27 +530,32 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* _
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mn = fmaxf(mn, sc[b][r]);
-      const float base = mn == -INFINITY ? 0.f : mn;  // no key of this half yet: every exponential is 0
-      l *= __builtin_amdgcn_exp2f((m - base) * cexp);
+      const float mcn = mn * cexp;
+      const float base = mn == -INFINITY ? 0.f : mcn;  // no key of this half yet: every exponential is 0
+      l *= __builtin_amdgcn_exp2f(mc - base);
       m = mn;
-      const float mc = base * cexp;
+      mc = mcn;
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f(fmaf(sc[b][r], cexp, -mc));
+        for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f(fmaf(sc[b][r], cexp, -base));
     }
     kb += 2;
   } while (kb < nkb);
-  // both halves' keys; p = exp2(s cexp - e) is then normalised
-  float e;
+  // both halves' keys; p = exp2(s cexp - e) is then normalised up to e's own
+  // rounding (of scores of 1e5 as large as bf16's), which `fix` takes out of O
+  float e, fix;
   {
-    const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(mc), __float_as_uint(mc), false, false);
     const auto rl = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
     const float m0 = __uint_as_float(rm[0]), m1 = __uint_as_float(rm[1]);
     const float mm = fmaxf(m0, m1);
-    const float lt = __uint_as_float(rl[0]) * __builtin_amdgcn_exp2f((m0 - mm) * cexp) +
-                     __uint_as_float(rl[1]) * __builtin_amdgcn_exp2f((m1 - mm) * cexp);
-    e = mm * cexp + __builtin_amdgcn_logf(lt);  // log2
+    const float lt = __uint_as_float(rl[0]) * __builtin_amdgcn_exp2f(m0 - mm) +
+                     __uint_as_float(rl[1]) * __builtin_amdgcn_exp2f(m1 - mm);
+    const float lg = __builtin_amdgcn_logf(lt);  // log2
+    e = mm + lg;
+    const float d = e - mm;
+    fix = __builtin_amdgcn_exp2f(-((mm - (e - d)) + (lg - d)));  // e + that difference is mm + lg exactly
   }
 
   // pass 2: bf16 probabilities times V
@@ -611,8 +618,8 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* _
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       uint16_t* yp = y0 + 32 * d + 8 * g;
-      const uint32_t u0 = pack_bf16(o[d][4 * g], o[d][4 * g + 1]);
-      const uint32_t u1 = pack_bf16(o[d][4 * g + 2], o[d][4 * g + 3]);
+      const uint32_t u0 = pack_bf16(o[d][4 * g] * fix, o[d][4 * g + 1] * fix);
+      const uint32_t u1 = pack_bf16(o[d][4 * g + 2] * fix, o[d][4 * g + 3] * fix);
       if (vec) {
         *(uint2*)yp = make_uint2(u0, u1);
       } else {
