@@ -425,7 +425,8 @@ __global__ void lin_plain_kernel(const uint16_t* __restrict__ X, int64_t ldx, co
 // the form before (64 queries per workgroup, 16-wide MFMA, P and V transposed
 // element by element through LDS), 569 us now (483 TFLOP/s of the two products).
 // The query blocks of one (sequence, head) run on one XCD and share its K and
-// V in that XCD's L2.
+// V in that XCD's L2, but for heads left over from groups of eight: one head (of
+// 128, 16384 tokens) on one XCD 1357 us, over all of them 608; nine heads 1558 and 1050.
 // ---------------------------------------------------------------------------
 typedef short s16v4 __attribute__((ext_vector_type(4)));
 typedef float f16x __attribute__((ext_vector_type(16)));
@@ -436,6 +437,11 @@ __device__ __forceinline__ f16x mma32_bf16(const u32x4& a, const u32x4& b, f16x 
   __builtin_memcpy(&bv, &b, 16);
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
 }
+
+// (Sequence, head) pairs left over from groups of eight, one per XCD; seven run as a
+// group (spread over all XCDs they read every K and V eight times: 5 % slower up to
+// 8192 tokens).
+__host__ __device__ inline int attn_left(int nsh) { return nsh % 8 == 7 ? 0 : nsh % 8; }
 
 template <int HD, int NW>
 __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* __restrict__ Q,
@@ -450,11 +456,22 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_kernel(const uint16_t* _
   constexpr int TILE = KB * CH;    // chunks per operand tile
   constexpr int NL = TILE / (64 * NW);  // 16-byte loads per thread, operand and block
   __shared__ u32x4 sm[2][2][TILE];  // [buffer][K, V]
-  // ids go round-robin over the XCDs: all query blocks of a head on one of them
-  const int x = (int)(blockIdx.x % 8), y = (int)(blockIdx.x / 8);
-  const int sh = (y / nqb) * 8 + x;
-  if (sh >= nsh) return;
-  const int qb = nqb - 1 - y % nqb;  // the longest query blocks first
+  // ids go round-robin over the XCDs: all query blocks of a head on one of them,
+  // the longest first; before that the heads that make no group (attn_left), spread
+  // over all XCDs, the shortest first where others follow (when all are resident a
+  // CU then holds long and short ones)
+  const int left = attn_left(nsh), off = (int)rup((int64_t)left * nqb, 8);
+  int id = (int)blockIdx.x, sh, qb;
+  if (id < off) {
+    if (id >= left * nqb) return;
+    sh = nsh - left + id % left;
+    qb = nsh < 8 ? nqb - 1 - id / left : id / left;
+  } else {
+    id = (id - off) / 8;
+    sh = id / nqb * 8 + (int)(blockIdx.x % 8);
+    if (sh >= nsh) return;
+    qb = nqb - 1 - id % nqb;
+  }
   const int h = sh % heads;
   const int64_t row0 = (int64_t)(sh / heads) * L;  // the sequence's first token
   const int col0 = h * HD;
@@ -773,7 +790,8 @@ duo_status duo_attention(const void* Q, const void* K, const void* V, int64_t ld
   // workgroups (512 in all), so that short or few sequences spread further
   const bool wide = (int64_t)nsh * cdiv(seq_len, 128) >= 512;
   const int nqb = (int)cdiv(seq_len, wide ? 128 : 64);
-  const dim3 grid((unsigned)(rup(nsh, 8) * nqb));
+  const int left = attn_left(nsh);
+  const dim3 grid((unsigned)(rup((int64_t)left * nqb, 8) + rup(nsh - left, 8) * nqb));
   const int vec = ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(O) & 7) == 0;
   auto go = [&](auto kern, int nw) {
     hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, s, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V, ld,

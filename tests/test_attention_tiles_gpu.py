@@ -57,6 +57,13 @@ def test_attention_tile_edges(duo_lib, nseq, L, heads, hd):
 
 
 @pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("nseq,heads", [(1, 5), (1, 7), (1, 8), (3, 3), (2, 7), (1, 15), (2, 8), (1, 41)])
+def test_attention_head_counts(duo_lib, nseq, heads, hd):
+    # (sequence, head) pairs in groups of eight, left over from them, and seven over
+    _run(duo_lib, nseq, 200, heads, hd, pad=0, ldo_odd=False)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
 def test_attention_strided_rows(duo_lib, hd):
     _run(duo_lib, 2, 100, 3, hd, pad=8, ldo_odd=True)
 
