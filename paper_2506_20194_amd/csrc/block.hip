@@ -337,52 +337,61 @@ __global__ __launch_bounds__(512) void lin256_kernel(const uint16_t* __restrict_
   pp_loop<HA, G::LW, G::LX>(nst, acc, issue, read_w, read_x);
 
   // accumulator element r of block (a, b): n = 2 HW wi + 16 a + 4 g + r, m = 64 wj + 16 b + l16
-  if (vec) {
-    // residual added in fp32, one rounding; staged through LDS, 128 tokens per
-    // pass, so that global accesses are 16 bytes per lane
+  // residual added in fp32, one rounding; staged through LDS, 128 tokens per pass,
+  // so that global accesses are 16 bytes per lane, or without `vec` (rows of Y or R
+  // that 16-byte accesses cannot take) consecutive in a wave.  (Straight from the
+  // accumulators, two bytes per row and lane: 65536 x 64 -> 300 with a residual 99 us,
+  // 46 here.)
 #pragma unroll
-    for (int h = 0; h < TM / 128; ++h) {
-      lds_barrier();
-      if (wj >> 1 == h)
+  for (int h = 0; h < TM / 128; ++h) {
+    lds_barrier();
+    if (wj >> 1 == h)
 #pragma unroll
-        for (int a = 0; a < 2 * HA; ++a)
+      for (int a = 0; a < 2 * HA; ++a)
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
-            *(f4*)(lsm + ((wj & 1) * 64 + b * 16 + l16) * G::ELS + (wi * 2 * G::HW + a * 16 + 4 * g) * 4) = acc[a][b];
-      lds_barrier();
-#pragma unroll 4
-      for (int q = tid; q < 128 * (kLinB / 8); q += 512) {
-        const int rr = q / (kLinB / 8), c8 = (q % (kLinB / 8)) * 8;
-        const int i = i0 + h * 128 + rr, j = j0 + c8;
-        if (i >= M || j >= N) continue;
-        const f4 v0 = *(const f4*)(lsm + rr * G::ELS + c8 * 4), v1 = *(const f4*)(lsm + rr * G::ELS + c8 * 4 + 16);
-        float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-        if (R) {
-          const u32x4 rv = *(const u32x4*)(R + (int64_t)i * ldr + j);
+        for (int b = 0; b < 4; ++b)
+          *(f4*)(lsm + ((wj & 1) * 64 + b * 16 + l16) * G::ELS + (wi * 2 * G::HW + a * 16 + 4 * g) * 4) = acc[a][b];
+    lds_barrier();
+    if (!vec) {
+      // a thread takes one column, every other row, sixteen rows' loads at a time
+      const int c = tid % kLinB, j = j0 + c, ib = i0 + h * 128 + tid / kLinB;
+      if (j >= N) continue;
+      const uint8_t* l = lsm + (tid / kLinB) * G::ELS + c * 4;
+      for (int q = 0; q < 64; q += 16) {
+        uint16_t rv[16];
+        if (R)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] += bf16_bits_to_f32((uint16_t)(rv[e >> 1] >> (16 * (e & 1))));
+          for (int e = 0; e < 16; ++e) rv[e] = R[(int64_t)min(ib + 2 * (q + e), M - 1) * ldr + j];
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = *(const float*)(l + 2 * (q + e) * G::ELS);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int i = ib + 2 * (q + e);
+          if (R) v[e] += bf16_bits_to_f32(rv[e]);
+          if (i < M) Y[(int64_t)i * ldy + j] = f32_to_bf16_bits(v[e]);
         }
-        u32x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
-        *(u32x4*)(Y + (int64_t)i * ldy + j) = o;
       }
+      continue;
     }
-    return;
-  }
+#pragma unroll 4
+    for (int q = tid; q < 128 * (kLinB / 8); q += 512) {
+      const int rr = q / (kLinB / 8), c8 = (q % (kLinB / 8)) * 8;
+      const int i = i0 + h * 128 + rr, j = j0 + c8;
+      if (i >= M || j >= N) continue;
+      const f4 v0 = *(const f4*)(lsm + rr * G::ELS + c8 * 4), v1 = *(const f4*)(lsm + rr * G::ELS + c8 * 4 + 16);
+      float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+      if (R) {
+        const u32x4 rv = *(const u32x4*)(R + (int64_t)i * ldr + j);
 #pragma unroll
-  for (int a = 0; a < 2 * HA; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + wj * 64 + b * 16 + l16, j = j0 + wi * 2 * G::HW + a * 16 + 4 * g + r;
-        if (i < M && j < N) {
-          float v = acc[a][b][r];
-          if (R) v += bf16_bits_to_f32(R[(int64_t)i * ldr + j]);
-          Y[(int64_t)i * ldy + j] = f32_to_bf16_bits(v);
-        }
+        for (int e = 0; e < 8; ++e) v[e] += bf16_bits_to_f32((uint16_t)(rv[e >> 1] >> (16 * (e & 1))));
       }
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
+      *(u32x4*)(Y + (int64_t)i * ldy + j) = o;
+    }
+  }
 }
 
 // Linear for rows that are not 16-byte aligned or K % 8 != 0: one thread per
@@ -724,13 +733,17 @@ duo_status duo_linear(const void* X, int64_t m, int64_t k, int64_t ldx, const vo
     // tile each; two of the 128 tiles) times a fixed part (launch, first loads,
     // epilogue) and a part per k, fitted to measured launches (m x k -> n: 4096 x
     // 4096 -> 4096 95, 57.5 x 2 and 181 us; 40000 x 512 -> 300 41, 46 and 38 us).
-    // The 128 tile keeps short sums and widths that fill 256 badly.
+    // The 128 tile keeps short sums and widths that fill 256 badly.  Two-byte
+    // stores cost a large tile 9 or 4.5 us, which nothing on the CU overlaps (65536 x 64
+    // -> 300 27 us on 128 tiles, 39 on 256; x 256 -> 777 80 and 91); a residual
+    // read two bytes at a time costs the 128 tile more (68 and 46; 167 and 105).
+    const int vy = n % 8 == 0 && ldy % 8 == 0 && aligned16(Y) && (!R || (ldr % 8 == 0 && aligned16(R)));
+    const double sc = vy || R ? 0.0 : 4.5;
     const int64_t t256 = cdiv(m, 256) * cdiv(n, kLinB), t128 = cdiv(m, 128) * cdiv(n, kLinB);
-    const double c256 = (double)cdiv(t256, 256) * (9.5 + 0.0213 * (double)k);
-    const double c128 = (double)cdiv(t128, 256) * (7.5 + 0.0122 * (double)k);
+    const double c256 = (double)cdiv(t256, 256) * (9.5 + 2.0 * sc + 0.0213 * (double)k);
+    const double c128 = (double)cdiv(t128, 256) * (7.5 + sc + 0.0122 * (double)k);
     const double cold = (double)cdiv(tiles, 512) * (7.8 + 0.0201 * (double)k);
     if (k % 64 == 0 && (c256 <= cold || c128 <= cold)) {
-      const int vy = n % 8 == 0 && ldy % 8 == 0 && aligned16(Y) && (!R || (ldr % 8 == 0 && aligned16(R)));
       auto go = [&](auto kern, int64_t nt, size_t lds) -> duo_status {
         if (nt > INT32_MAX) return DUO_ERR_UNSUPPORTED;
         if (duo_status st = set_max_lds((const void*)kern, lds); st != DUO_OK) return st;

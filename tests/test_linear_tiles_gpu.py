@@ -39,6 +39,14 @@ def test_linear_large_tiles(duo_lib, m, k, n):
     _run(duo_lib, m, k, n, res=True, inplace=True)
 
 
+# rows of Y or R that 16-byte accesses cannot take, on the large tiles
+@pytest.mark.parametrize("m,n", [(129, 257), (300, 1003), (4097, 4001), (3839, 300)])
+def test_linear_large_tiles_narrow_stores(duo_lib, m, n):
+    _run(duo_lib, m, 1024, n, res=False)
+    _run(duo_lib, m, 1024, n, res=True)
+    _run(duo_lib, m, 128, n, res=True, inplace=True)
+
+
 @pytest.mark.parametrize("m,k,n", [(1, 64, 8), (300, 4096, 520), (257, 72, 256), (255, 128, 257), (4000, 128, 300)])
 def test_linear_small_tiles(duo_lib, m, k, n):
     _run(duo_lib, m, k, n, res=True)
