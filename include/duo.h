@@ -107,8 +107,8 @@ typedef struct {
 } duo_chol_info;
 
 /* Bytes of workspace an operation needs (0 for a bad op).  Pure host
- * arithmetic; safe to call without a device.  For DUO_OP_SCORE_TERMS and
- * _PRUNE_LAYER the size includes packed operands of the large products; a
+ * arithmetic; safe to call without a device.  For DUO_OP_PRUNE_LAYER the size
+ * includes packed operands of the large products (Y form, unquantised); a
  * workspace too small for those but large enough for the rest is accepted, and
  * the products it has no room for run on another path (fp32 instructions,
  * slower, last bits may differ). */

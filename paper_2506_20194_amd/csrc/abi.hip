@@ -119,7 +119,7 @@ size_t duo_workspace_size(int32_t op, int64_t n, int64_t k, int64_t m, int32_t b
   switch (op) {
     case DUO_OP_HESSIAN: return hessian_ws_bytes(m < 1 ? 1 : m, k);
     case DUO_OP_CHOL_INV: return chol_ws_bytes(k);
-    case DUO_OP_SCORE_TERMS: return score_ws_bytes(k) + score_pk_bytes(k);
+    case DUO_OP_SCORE_TERMS: return score_ws_bytes(k);
     case DUO_OP_SWEEP:
       if (n < 1 || block < 1 || block > kMaxBlock) return 0;
       return sweep_ws_bytes(n, k, block);
@@ -241,9 +241,7 @@ duo_status duo_score_terms(const float* L, int64_t ldl, const float* G, int64_t 
   duo_status d = device_ok();
   if (d != DUO_OK) return d;
   prof_begin(DUO_PROF_SCORE, (hipStream_t)stream);
-  const size_t base = score_ws_bytes(k);
-  duo_status r = score_run(L, ldl, G, ldg, a, k, D, ldd, fac, ws, (uint8_t*)ws + base, ws_bytes - base,
-                           (hipStream_t)stream);
+  duo_status r = score_run(L, ldl, G, ldg, a, k, D, ldd, fac, ws, nullptr, 0, (hipStream_t)stream);
   prof_end(DUO_PROF_SCORE, (hipStream_t)stream);
   return r;
 }
@@ -313,10 +311,12 @@ duo_status duo_prune_layer(const void* W, int32_t w_dtype, int64_t n, int64_t k,
   // k^3 / 3 of D but launches two more products per block (measured at
   // n = k = 4096: 0.17 ms slower per layer; k = 11008: 2 ms faster).
   const bool yform = o.form == DUO_FORM_Y || (o.form == DUO_FORM_AUTO && y_ok && k >= kYFormMinK);
+  // Split products only in the unquantised Y form.  A quantised value may round to
+  // the next code when a last bit of what it is computed from differs, so
+  // quantised layers keep the fp32 instructions; and the D form gives the bits
+  // of duo_score_terms and duo_sweep, which do not know whether the layer is quantised.
   void* const pk = (uint8_t*)ws + pw.bytes;
-  // A quantised value may round to the next code when a last bit of what it is
-  // computed from differs; quantised layers keep the fp32 instructions.
-  const size_t pk_bytes = o.q_bits ? 0 : ws_bytes - pw.bytes;
+  const size_t pk_bytes = o.q_bits || !yform ? 0 : ws_bytes - pw.bytes;
   prof_begin(DUO_PROF_SCORE, s);
   duo_status r = score_run(L, ldl, G, ldg, a, k, yform ? nullptr : w.D, k, w.fac, w.score, pk, pk_bytes, s);
   prof_end(DUO_PROF_SCORE, s);
@@ -327,7 +327,7 @@ duo_status duo_prune_layer(const void* W, int32_t w_dtype, int64_t n, int64_t k,
                   mask_out, block_scores_out, w.sweep, pk, pk_bytes, s, score_u(w.score, k), k, w.D);
   else
     r = sweep_run(W, w_dtype, n, k, ldw, L, ldl, w.D, k, w.fac, w_sparsity, o, block, mask_in, W_out, W_out_lowp,
-                  mask_out, block_scores_out, w.sweep, pk, pk_bytes, s);
+                  mask_out, block_scores_out, w.sweep, nullptr, 0, s);
   prof_end(DUO_PROF_SWEEP, s);
   return r;
 }

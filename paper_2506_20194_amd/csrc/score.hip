@@ -92,7 +92,7 @@ duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, c
   d.order = ORDER_DIAG;  // K range [i0, j0 + 128): grows with the distance from the diagonal
   d.nterms = 1;
   d.t[0] = GemmTerm{w.Q, k, 1, L, ldl, 0, (int)k, 1.f, KLO_ROW, KHI_COL};
-  return gemm_f32_split(d, pk, pk_bytes, s, ZERO_UPTO);  // U is strictly upper
+  return gemm_f32(d, s);
 }
 
 }  // namespace duo
