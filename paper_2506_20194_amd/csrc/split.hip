@@ -133,14 +133,16 @@ struct SplitArgs {
   float alpha[2], beta;
   int tri, klo, khi, order, dual, vec;
   int ngc, ngr;   // groups of 4 tile columns, of 8 tile rows
+  int rot;        // second product of a dual one: its first group's XCD is 8 - rot
 };
 
 // Tile of a workgroup.  An XCD takes groups of 8 x 4 tiles (its 32 CUs: 12 operand
 // panels for 32 tiles in its L2), the groups in order of falling cost: by column
 // group from the first (K range [j0, K)) or the last ([0, j0 + 256)), by row group
-// from the first ([i0, K)).
+// from the first ([i0, K)).  A dual product's second part goes on with the XCD after
+// the last group of the first (2048 x 5120: five XCDs had two groups each).
 __device__ inline bool split_tile(const SplitArgs& A, int* ti, int* tj) {
-  const int x = blockIdx.x % 8, y = blockIdx.x / 8;
+  const int x = (blockIdx.x + (A.dual ? blockIdx.y * A.rot : 0)) % 8, y = blockIdx.x / 8;
   int g = (y / 32) * 8 + x;
   const int in = y % 32;
   int gc, gr;
@@ -311,39 +313,48 @@ size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products) {
   return align_up((packed_bytes(M, K) + packed_bytes(N, K)) * (size_t)products);
 }
 
+// Tiles that the fullest XCD takes of a whole (not triangular) product's.
+static int64_t xcd_tiles(int64_t M, int64_t N, int np) {
+  const int64_t tm = cdiv(M, ST), tn = cdiv(N, ST);
+  int64_t x[8] = {}, g = 0;
+  for (int p = 0; p < np; ++p)
+    for (int64_t c = 0; c < tn; c += 4)
+      for (int64_t r = 0; r < tm; r += 8) x[g++ % 8] += std::min<int64_t>(8, tm - r) * std::min<int64_t>(4, tn - c);
+  return *std::max_element(x, x + 8);
+}
+
 // Whether a product takes this path: its time by measured rates against that of
-// gemm_f32.  Here a CU adds 64 k to a 256 tile in 8.6 us (1500 TFLOP/s of bf16) and
-// loses 22 us per tile to its first loads and to reading and writing C, and packing
-// moves 10 bytes per element at 4 TB/s, 6 us per launch; the last tile to finish may
-// be the one with the longest sum.  There 110 TFLOP/s (64-wide tiles, the sizes where
-// the choice is close) and a launch.  At n = 4096: k = 4096 stays on fp32
-// instructions (with this path for Q and D 4.55 against 4.12 ms per solve), k = 8192
-// 15.2 -> 14.5 ms, k = 11008 28.0 -> 24.5 ms (with the factorisation
-// on this path too, which needs the same bits for quantised layers and is not); n = 8192, k = 28672, score and
-// sweep alone, 308 -> 247 ms.
+// gemm_f32.  Packing moves 10 bytes per element at 4 TB/s, 6 us per launch.
+// Two products in one launch (K = 1024, n x N each): a round of the 32 CUs of an XCD
+// takes 8.3 us per 64 k, against 105 TFLOP/s and a launch: measured 2048 x 5120 345
+// and 370 us, 2560 x 4096 295 and 372, but 1536 x 5120 289 and 283, 2304 x 3072 276 and 260;
+// of 143 sizes from 512 x 1024 to 8192 x 10240 these take the slower path at three, by 2 %
+// at most.  In the sweep, where C has left the caches, the path lost up to 2 % of
+// whole solves at k = 6144 where it should have gained 10 % of the product: hence the 1.2.
+// (Solves at n = 2048: k = 6144 3.48 -> 3.37 ms, 8192 5.80 -> 5.19, 9216 7.20 -> 6.18.)
+// The score product (upper tiles, shrinking sums): 8.6 us per 64 k and 22 us per
+// round of 256 tiles, the last tile to finish may be the one with the longest sum,
+// against 110 TFLOP/s: k = 4096 405 and 252 us, 8192 1204 and 1444, 11008 2426 and 3408.
 static bool split_pays(const GemmDesc& d) {
-  if (d.inplace || d.tri == TRI_LOWER || (d.nterms == 2 && !d.dual)) return false;
-  const int64_t tm = cdiv(d.M, ST), tn = cdiv(d.N, ST);
+  if (d.inplace || d.batch > 1 || (d.nterms == 2 && !d.dual)) return false;
   const int np = d.dual ? 2 : 1;
-  const double nb = d.batch > 1 ? d.batch : 1;
-  const double tiles = (double)(d.tri == TRI_ALL ? tm * tn : tm * (tm + 1) / 2) * nb;
-  const double area = (d.tri == TRI_ALL ? (double)d.M * d.N : 0.5 * d.M * d.N) * nb;
-  double sum_k = 0.0, max_k = 0.0, flop = 0.0, packed = 0.0;
-  for (int i = 0; i < np; ++i) {
-    const GemmTerm& t = d.t[i];
-    if (!t.a_row || t.K < 256) return false;
-    // average length of the sums: whole, or shrinking to nothing along one side
-    // (along a side of the triangle of tiles: a third)
-    const bool whole = t.klo == KLO_ZERO && t.khi == KHI_FULL;
-    const double frac = whole ? 1.0 : d.tri == TRI_ALL ? 0.5 : 1.0 / 3.0;
-    sum_k += tiles * frac * t.K;
-    max_k = std::max(max_k, (double)t.K);
-    flop += 2.0 * area * frac * t.K;
-    packed += ((double)d.M + (t.A == t.B ? 0 : d.N)) * t.K * (whole ? 1.0 : 0.75) * nb;
+  const int64_t K = d.t[0].K;
+  for (int i = 0; i < np; ++i)
+    if (!d.t[i].a_row || d.t[i].K != K || K < 256) return false;
+  const double pack = 10.0 / 4e12, launch = 6e-6, step = (double)cdiv(K, 64);
+  if (d.tri == TRI_ALL && d.t[0].klo == KLO_ZERO && d.t[0].khi == KHI_FULL) {
+    const double split = (double)cdiv(xcd_tiles(d.M, d.N, np), 32) * step * 8.3e-6 +
+                         np * ((double)(d.M + d.N) * K * pack + 2 * launch);
+    return 1.2 * split < 2.0 * np * d.M * d.N * K / 105e12 + launch;
   }
-  const double split = std::max(sum_k / 256.0, max_k) / 64.0 * 8.6e-6 + std::ceil(tiles * np / 256.0) * 22e-6 +
-                       packed * 10.0 / 4e12 + np * 12e-6;
-  return split < flop / 110e12 + 6e-6;
+  if (d.tri == TRI_UPPER && d.t[0].klo == KLO_COL && d.t[0].khi == KHI_FULL && np == 1) {
+    const int64_t tm = cdiv(d.M, ST), tiles = tm * (tm + 1) / 2;
+    const double sum_k = (double)tiles / 3.0 * K;
+    const double split = std::max(sum_k / 256.0, (double)K) / 64.0 * 8.6e-6 + (double)cdiv(tiles, 256) * 22e-6 +
+                         0.75 * (d.M + d.N) * K * pack + 2 * launch;
+    return split < (double)d.M * d.N / 3.0 * K / 110e12 + launch;
+  }
+  return false;
 }
 
 duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s, int zero_a, int zero_b) {
@@ -402,6 +413,7 @@ duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStrea
     groups = 0;
     for (int c = 0; c < A.ngc; ++c) groups += c / 2 + 1;
   }
+  A.rot = (int)(8 - groups % 8) % 8;
   if (duo_status st = set_max_lds((const void*)split_gemm_kernel, kLds); st != DUO_OK) return st;
   hipLaunchKernelGGL(split_gemm_kernel, dim3((unsigned)(rup(groups, 8) * 32), (unsigned)(d.dual ? 2 : nb)), dim3(512),
                      kLds, s, A);
