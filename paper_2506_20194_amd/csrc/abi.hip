@@ -54,12 +54,15 @@ PruneWs carve_prune(void* ws, int64_t n, int64_t k, int B) {
   return w;
 }
 
-// packed operands of the split products of duo_prune_layer, after carve_prune's part
-size_t prune_pk_bytes(int64_t n, int64_t k, int B) { return std::max(score_pk_bytes(k), sweep_pk_bytes(n, k, B)); }
-
 bool k_ok(int64_t k) { return k >= 1 && k <= kMaxK; }
 
 constexpr int64_t kYFormMinK = 6144;  // DUO_FORM_AUTO: the Y form from this k up
+
+// packed operands of the split products of duo_prune_layer, after carve_prune's part;
+// none where only a caller that asks for the Y form would use them
+size_t prune_pk_bytes(int64_t n, int64_t k, int B) {
+  return k < kYFormMinK ? 0 : align_up(std::max(score_pk_bytes(k), sweep_pk_bytes(n, k, B)));
+}
 
 }  // namespace
 

@@ -89,17 +89,14 @@ enum { ORDER_XCD = 0, ORDER_PLAIN = 1, ORDER_DIAG = 2 };
 duo_status gemm_f32(const GemmDesc& d, hipStream_t s);
 
 // ---- fp32 products on the bf16 matrix cores (split.hip) ----
-// gemm_f32 for products large enough to gain from it, else gemm_f32 itself.  pk:
-// scratch for the packed operands, split_bytes(M, N, K, products) of the largest
-// product (dual and batched ones: their number); with less, gemm_f32 runs.
-// With TRI_UPPER, C's diagonal 256 x 256 tiles are written whole.
-// zero_a, zero_b: entries of a one-term product's operands that count as zero
-// whatever is stored there (the tiles are 256 wide, and inside a 256-wide diagonal
-// tile the 128-wide block below (above) the diagonal need not hold zeros).
-enum { ZERO_NONE = 0, ZERO_BELOW = 1, ZERO_UPTO = 2 };  // l < r, l <= r (r: i of A, j of B)
-size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products);
-duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s, int zero_a = ZERO_NONE,
-                          int zero_b = ZERO_NONE);
+// gemm_f32, on the bf16 matrix cores where that pays (split_pays): a dual product
+// with whole sums (the Y form's lazy updates), or C = A B over the upper tiles with
+// sums from the tile's column on (the score product), of which the upper triangle
+// of A and the lower one of B count whatever is stored in the others, and C's diagonal
+// 256 x 256 tiles are written whole.  pk: scratch for the packed operands, split_bytes
+// (0 where gemm_f32 is the faster one; by sizes and forms alone); with less, gemm_f32 runs.
+size_t split_bytes(const GemmDesc& d);
+duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s);
 
 // ---- stage 2 (chol.hip) ----
 struct CholStatus {

@@ -3,8 +3,9 @@
 //   Q = G L            only the upper triangle (incl. diagonal) is needed;
 //   b_p = sum_{i>p} Q_pi^2, c_p = Q_pp / L_pp, fac_p = 1/L_pp^2 + a_p - b_p + 2 c_p;
 //   U = strict upper(Q); D = U L^T (strictly upper).
-// Both products run on the fp32 MFMA GEMM with tile-granular triangular K
-// ranges; fac uses fixed-order double sums.
+// Both products have tile-granular triangular K ranges: D's runs on the fp32 MFMA
+// GEMM, Q's for the Y form of the sweep on the split products (split.hip) where
+// they are faster.  fac uses fixed-order double sums.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -55,28 +56,32 @@ ScoreWs carve(void* ws, int64_t k) {
   return w;
 }
 
-}  // namespace
-
-size_t score_ws_bytes(int64_t k) { return carve(nullptr, k).bytes; }
-size_t score_pk_bytes(int64_t k) { return split_bytes(k, k, k, 1); }
-
-const float* score_u(const void* ws, int64_t k) { return carve(const_cast<void*>(ws), k).Q; }
-
-duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k, float* D,
-                     int64_t ldd, float* fac, void* ws, void* pk, size_t pk_bytes, hipStream_t s) {
-  const ScoreWs w = carve(ws, k);
-  // Q = G L on upper tiles; L[l][i] = 0 for l < i, so l starts at the tile column
+// Q = G L on upper tiles; L[l][i] = 0 for l < i, so l starts at the tile column
+GemmDesc q_product(const float* L, int64_t ldl, const float* G, int64_t ldg, int64_t k, float* Q) {
   GemmDesc q{};
   q.M = (int)k;
   q.N = (int)k;
-  q.C = w.Q;
+  q.C = Q;
   q.ldc = k;
   q.beta = 0.f;
   q.tri = TRI_UPPER;
   q.order = ORDER_PLAIN;  // K range [j0, k): the first columns are the longest
   q.nterms = 1;
   q.t[0] = GemmTerm{G, ldg, 1, L, ldl, 1, (int)k, 1.f, KLO_COL, KHI_FULL};
-  duo_status st = gemm_f32_split(q, pk, pk_bytes, s, ZERO_BELOW, ZERO_BELOW);  // G's upper triangle, L's lower
+  return q;
+}
+
+}  // namespace
+
+size_t score_ws_bytes(int64_t k) { return carve(nullptr, k).bytes; }
+size_t score_pk_bytes(int64_t k) { return split_bytes(q_product(nullptr, k, nullptr, k, k, nullptr)); }
+
+const float* score_u(const void* ws, int64_t k) { return carve(const_cast<void*>(ws), k).Q; }
+
+duo_status score_run(const float* L, int64_t ldl, const float* G, int64_t ldg, const float* a, int64_t k, float* D,
+                     int64_t ldd, float* fac, void* ws, void* pk, size_t pk_bytes, hipStream_t s) {
+  const ScoreWs w = carve(ws, k);
+  duo_status st = gemm_f32_split(q_product(L, ldl, G, ldg, k, w.Q), pk, pk_bytes, s);
   if (st != DUO_OK) return st;
   hipLaunchKernelGGL(fac_kernel, dim3((unsigned)k), dim3(256), 0, s, w.Q, (int64_t)k, L, ldl, a, (int)k, fac);
   DUO_LAUNCH_CHECK();

@@ -1,8 +1,8 @@
 // fp32 products on the bf16 matrix cores.  Each fp32 operand is split exactly into
 // three bf16 parts, x = h + m + l (8 significant bits each, round to nearest), and
 //   a b = l_a h_b + h_a l_b + m_a m_b + m_a h_b + h_a m_b + h_a h_b
-// is accumulated in fp32, smallest terms first; the three terms left out are
-// below 2^-25 |a b|.  A term is exact, and per 64 k the accumulators are rounded
+// is accumulated in fp32, smallest terms first; of the three terms left out m_a l_b and
+// l_a m_b reach 2^-25 |a b| each (measured below).  A term is exact, and per 64 k the accumulators are rounded
 // 12 times where v_mfma_f32_16x16x4_f32 rounds them 16 times.  Six bf16 products at
 // about 1500 TFLOP/s are an fp32 product at 250, against 125-137 on the fp32 matrix
 // instructions (157 peak).
@@ -13,9 +13,10 @@
 // once and zero-fills rows to 256 and k to 64, so any size takes this path.
 //
 // Values: an operand that bf16 would round to infinity keeps the largest finite
-// h (m and l take the rest).  An infinite operand gives NaN where fp32 might give
-// an infinity (inf h + inf m); parts below 2^-126 (of operands below 2^-110) may be
-// flushed, an absolute error of 2^-126 |b|.
+// h (m and l take the rest).  An infinite operand gives NaN (inf m + inf l), where
+// fp32 gives an infinity or, if a zero of the triangle meets it, NaN.  Parts below
+// 2^-126 are rounded to multiples of 2^-133, an absolute error of up to 2^-134 |b|: less
+// than fp32's own rounding for operands above 2^-110.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,19 +33,14 @@ constexpr int ST = 256;                 // tile edge
 constexpr int kUnit = 128 * 128;        // bytes of an LDS unit: 128 rows x 64 k
 constexpr size_t kLds = (size_t)8 * kUnit;
 
-// What of an operand is read (tile-granular) and which entries count as zero:
-// r = its row (i of A, j of B), l = the contraction index.
-enum { NEED_ALL = 0, NEED_FROM = 1, NEED_UPTO = 2 };  // all; l >= tile start of r; l < tile end of r
-
 struct PackArgs {
   const float* src;  // element (r, l) at src[r * ld + l] (kc) or src[l * ld + r]
   int64_t ld;
   int kc, rows, K, rp, nkb;  // rp: rows padded to 256; nkb: k blocks of 32 (even)
-  int need, zero;
+  int tri;  // entries l < r count as zero, whatever is stored there
   int vec;
   uint8_t* dst;
   int64_t plane;   // bytes per plane
-  int64_t s_src, s_dst;  // per batch entry: elements, bytes
 };
 
 __device__ __forceinline__ uint32_t bits(float f) { return __float_as_uint(f); }
@@ -76,20 +72,19 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t
 constexpr int KPB = 4;
 __global__ __launch_bounds__(256) void pack_kernel(PackArgs A) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const float* src = A.src + blockIdx.z * A.s_src;
-  uint8_t* dst = A.dst + blockIdx.z * A.s_dst;
+  const float* src = A.src;
   // k-contiguous: 4 lanes cover 128 bytes of a row; else lanes along the rows
   const int r = blockIdx.x * 64 + (A.kc ? wave * 16 + (lane >> 2) : lane), g = A.kc ? lane & 3 : wave;
   const int t0 = (int)(blockIdx.x * 64) / ST * ST;
   const int rc = min(r, A.rows - 1);
   // the contraction indices of row r that do not count as zero (a chain of
   // conditions per entry in the place of these bounds was miscompiled by ROCm 7.2)
-  const int lo = A.zero == ZERO_BELOW ? r : A.zero == ZERO_UPTO ? r + 1 : 0;
+  const int lo = A.tri ? r : 0;
   const int hi = r >= A.rows ? 0 : A.K;
   for (int q = 0; q < KPB; ++q) {
     const int kb = blockIdx.y * KPB + q;
     if (kb >= A.nkb) break;
-    if ((A.need == NEED_FROM && kb * 32 + 32 <= t0) || (A.need == NEED_UPTO && kb * 32 >= t0 + ST)) continue;
+    if (A.tri && kb * 32 + 32 <= t0) continue;  // read by no tile
     const int l0 = kb * 32 + g * 8;
     float x[8];
     if (A.kc && A.vec && l0 + 8 <= A.K) {
@@ -113,7 +108,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs A) {
       m[e] = mm;
       l[e] = ll;
     }
-    uint8_t* d = dst + ((int64_t)(kb * 4 + g) * A.rp + r) * 16;
+    uint8_t* d = A.dst + ((int64_t)(kb * 4 + g) * A.rp + r) * 16;
     *(u32x4*)d = h;
     *(u32x4*)(d + A.plane) = m;
     *(u32x4*)(d + 2 * A.plane) = l;
@@ -121,25 +116,23 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs A) {
 }
 
 struct SplitArgs {
-  // packed operands of up to two products (dual: blockIdx.y selects) or of a batch
+  // packed operands of up to two products (dual: blockIdx.y selects)
   const uint8_t* pr[2];  // rows operand (A), mp rows
   const uint8_t* pc[2];  // columns operand (B), np rows
   int64_t plane_r[2], plane_c[2];
-  int64_t s_r, s_c, s_C;  // per batch entry: bytes, bytes, elements
   float* C[2];
   int64_t ldc;
   int M, N, mp, np;
   int K[2];       // padded to 64
   float alpha[2], beta;
-  int tri, klo, khi, order, dual, vec;
+  int tri, klo, dual, vec;
   int ngc, ngr;   // groups of 4 tile columns, of 8 tile rows
   int rot;        // second product of a dual one: its first group's XCD is 8 - rot
 };
 
 // Tile of a workgroup.  An XCD takes groups of 8 x 4 tiles (its 32 CUs: 12 operand
-// panels for 32 tiles in its L2), the groups in order of falling cost: by column
-// group from the first (K range [j0, K)) or the last ([0, j0 + 256)), by row group
-// from the first ([i0, K)).  A dual product's second part goes on with the XCD after
+// panels for 32 tiles in its L2), by column group: with KLO_COL (K range [j0, K)) the
+// first are the longest.  A dual product's second part goes on with the XCD after
 // the last group of the first (2048 x 5120: five XCDs had two groups each).
 __device__ inline bool split_tile(const SplitArgs& A, int* ti, int* tj) {
   const int x = (blockIdx.x + (A.dual ? blockIdx.y * A.rot : 0)) % 8, y = blockIdx.x / 8;
@@ -154,14 +147,8 @@ __device__ inline bool split_tile(const SplitArgs& A, int* ti, int* tj) {
     gr = g;
   } else {
     if (g >= A.ngc * A.ngr) return false;
-    if (A.klo == KLO_ROW) {
-      gr = g / A.ngc;
-      gc = g % A.ngc;
-    } else {
-      gc = g / A.ngr;
-      gr = g % A.ngr;
-      if (A.khi == KHI_COL) gc = A.ngc - 1 - gc;
-    }
+    gc = g / A.ngr;
+    gr = g % A.ngr;
   }
   *ti = gr * 8 + in % 8;
   *tj = gc * 4 + in / 8;
@@ -180,10 +167,8 @@ __global__ __launch_bounds__(512) void split_gemm_kernel(SplitArgs A) {
   int ti, tj;
   if (!split_tile(A, &ti, &tj)) return;
   const int pb = A.dual ? (int)blockIdx.y : 0;
-  const int64_t z = A.dual ? 0 : blockIdx.y;
   const int i0 = ti * ST, j0 = tj * ST;
-  const int klo = A.klo == KLO_ROW ? i0 : A.klo == KLO_COL ? j0 : 0;
-  const int khi = min(A.khi == KHI_ROW ? i0 + ST : A.khi == KHI_COL ? j0 + ST : A.K[pb], A.K[pb]);
+  const int klo = A.klo == KLO_COL ? j0 : 0, khi = A.K[pb];
   int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wi = wave >> 2, wj = wave & 3;
@@ -197,8 +182,8 @@ __global__ __launch_bounds__(512) void split_gemm_kernel(SplitArgs A) {
     // w % 4), 64 unit rows per load; unit row u is tile column 128 (u / 64) + 64 h + u % 64
     // for half h, tile row 64 (u / 32) + 32 h + u % 32.
     const int uw = __builtin_amdgcn_readfirstlane(wave);
-    const uint8_t* const uc = A.pc[pb] + z * A.s_c + ((int64_t)(klo / 8 + uw) * A.np + j0) * 16;
-    const uint8_t* const ur = A.pr[pb] + z * A.s_r + ((int64_t)(klo / 8 + uw) * A.mp + i0) * 16;
+    const uint8_t* const uc = A.pc[pb] + ((int64_t)(klo / 8 + uw) * A.np + j0) * 16;
+    const uint8_t* const ur = A.pr[pb] + ((int64_t)(klo / 8 + uw) * A.mp + i0) * 16;
     const int64_t kc = (int64_t)A.np * 128, kr = (int64_t)A.mp * 128;  // bytes per 64 k
     const int64_t plc = A.plane_c[pb], plr = A.plane_r[pb];
     const uint32_t lc = lane * 16, lr = (64 * (lane >> 5) + (lane & 31)) * 16;
@@ -236,7 +221,7 @@ __global__ __launch_bounds__(512) void split_gemm_kernel(SplitArgs A) {
   }
   // C = beta C + alpha acc; element r of block (a, b) is row 64 wj + 16 b + lane % 16,
   // column 128 wi + 16 a + 4 (lane / 16) + r
-  float* C = A.C[pb] + z * A.s_C + (int64_t)i0 * A.ldc + j0;
+  float* C = A.C[pb] + (int64_t)i0 * A.ldc + j0;
   const float al = A.alpha[pb], be = A.beta;
   const int rows = min(ST, A.M - i0), cols = min(ST, A.N - j0);
   const int r0 = wj * 64 + (lane & 15), c0 = wi * 128 + 4 * (lane >> 4);
@@ -284,8 +269,7 @@ bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 size_t packed_bytes(int64_t rows, int64_t K) { return (size_t)rup(rows, ST) * rup(K, 64) * 6; }
 
-duo_status pack(const float* src, int64_t ld, int kc, int rows, int K, int need, int zero, int nb, int64_t s_src,
-                uint8_t* dst, int64_t s_dst, hipStream_t s) {
+duo_status pack(const float* src, int64_t ld, int kc, int rows, int K, int tri, uint8_t* dst, hipStream_t s) {
   PackArgs p{};
   p.src = src;
   p.ld = ld;
@@ -294,24 +278,16 @@ duo_status pack(const float* src, int64_t ld, int kc, int rows, int K, int need,
   p.K = K;
   p.rp = (int)rup(rows, ST);
   p.nkb = (int)rup(K, 64) / 32;
-  p.need = need;
-  p.zero = zero;
-  p.vec = al16(src) && ld % 4 == 0 && s_src % 4 == 0;
+  p.tri = tri;
+  p.vec = al16(src) && ld % 4 == 0;
   p.dst = dst;
   p.plane = (int64_t)p.rp * p.nkb * 64;
-  p.s_src = s_src;
-  p.s_dst = s_dst;
-  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)(p.rp / 64), (unsigned)cdiv(p.nkb, KPB), (unsigned)nb), dim3(256), 0, s,
-                     p);
+  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)(p.rp / 64), (unsigned)cdiv(p.nkb, KPB)), dim3(256), 0, s, p);
   DUO_LAUNCH_CHECK();
   return DUO_OK;
 }
 
 }  // namespace
-
-size_t split_bytes(int64_t M, int64_t N, int64_t K, int64_t products) {
-  return align_up((packed_bytes(M, K) + packed_bytes(N, K)) * (size_t)products);
-}
 
 // Tiles that the fullest XCD takes of a whole (not triangular) product's.
 static int64_t xcd_tiles(int64_t M, int64_t N, int np) {
@@ -357,42 +333,31 @@ static bool split_pays(const GemmDesc& d) {
   return false;
 }
 
-duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s, int zero_a, int zero_b) {
-  const int nb = d.batch > 1 ? d.batch : 1, np = d.dual ? 2 : 1;
-  size_t need = 0;
-  for (int i = 0; i < np; ++i) need += (packed_bytes(d.M, d.t[i].K) + packed_bytes(d.N, d.t[i].K)) * nb;
-  if (!split_pays(d) || need > pk_bytes) return gemm_f32(d, s);
+size_t split_bytes(const GemmDesc& d) {
+  if (!split_pays(d)) return 0;
+  return (packed_bytes(d.M, d.t[0].K) + packed_bytes(d.N, d.t[0].K)) * (d.dual ? 2 : 1);
+}
+
+duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStream_t s) {
+  const int np = d.dual ? 2 : 1;
+  const size_t need = split_bytes(d);
+  if (need == 0 || need > pk_bytes) return gemm_f32(d, s);
   SplitArgs A{};
   uint8_t* at = (uint8_t*)pk;
+  const bool tri = d.tri == TRI_UPPER;
   for (int i = 0; i < np; ++i) {
     const GemmTerm& t = d.t[i];
-    const size_t ba = packed_bytes(d.M, t.K), bb = packed_bytes(d.N, t.K);
-    // (upper tiles: a range from the tile's column on lies at or past its row)
-    const int na = t.klo == KLO_ROW || (d.tri == TRI_UPPER && t.klo == KLO_COL) ? NEED_FROM
-                   : t.khi == KHI_ROW                                           ? NEED_UPTO
-                                                                                : NEED_ALL;
-    const int nc = t.klo == KLO_COL ? NEED_FROM : t.khi == KHI_COL ? NEED_UPTO : NEED_ALL;
-    const bool same = t.A == t.B && t.lda == t.ldb && !t.b_row && d.M == d.N && na == nc && zero_a == zero_b;
-    uint8_t* pa = at;
-    at += ba * nb;
-    uint8_t* pb = same ? pa : at;
-    if (!same) at += bb * nb;
-    if (duo_status st = pack(t.A, t.lda, 1, d.M, t.K, na, zero_a, nb, d.sA[i], pa, (int64_t)ba, s); st != DUO_OK)
-      return st;
-    if (!same)
-      if (duo_status st = pack(t.B, t.ldb, !t.b_row, d.N, t.K, nc, zero_b, nb, d.sB[i], pb, (int64_t)bb, s);
-          st != DUO_OK)
-        return st;
-    A.pr[i] = pa;
-    A.pc[i] = pb;
+    A.pr[i] = at;
+    if (duo_status st = pack(t.A, t.lda, 1, d.M, t.K, tri, at, s); st != DUO_OK) return st;
+    at += packed_bytes(d.M, t.K);
+    A.pc[i] = at;
+    if (duo_status st = pack(t.B, t.ldb, !t.b_row, d.N, t.K, tri, at, s); st != DUO_OK) return st;
+    at += packed_bytes(d.N, t.K);
     A.K[i] = (int)rup(t.K, 64);
     A.plane_r[i] = (int64_t)rup(d.M, ST) * A.K[i] * 2;
     A.plane_c[i] = (int64_t)rup(d.N, ST) * A.K[i] * 2;
-    A.s_r = (int64_t)ba;
-    A.s_c = (int64_t)bb;
     A.alpha[i] = t.alpha;
   }
-  A.s_C = d.sC;
   A.C[0] = d.C;
   A.C[1] = d.C2;
   A.ldc = d.ldc;
@@ -403,20 +368,18 @@ duo_status gemm_f32_split(const GemmDesc& d, void* pk, size_t pk_bytes, hipStrea
   A.beta = d.beta;
   A.tri = d.tri;
   A.klo = d.t[0].klo;
-  A.khi = d.t[0].khi;
   A.dual = d.dual;
-  A.vec = d.ldc % 4 == 0 && d.N % 4 == 0 && al16(d.C) && (!d.dual || al16(d.C2)) && (nb == 1 || d.sC % 4 == 0);
+  A.vec = d.ldc % 4 == 0 && d.N % 4 == 0 && al16(d.C) && (!d.dual || al16(d.C2));
   A.ngc = (int)cdiv(cdiv(d.N, ST), 4);
   A.ngr = (int)cdiv(cdiv(d.M, ST), 8);
   int64_t groups = (int64_t)A.ngc * A.ngr;
-  if (d.tri == TRI_UPPER) {
+  if (tri) {
     groups = 0;
     for (int c = 0; c < A.ngc; ++c) groups += c / 2 + 1;
   }
   A.rot = (int)(8 - groups % 8) % 8;
   if (duo_status st = set_max_lds((const void*)split_gemm_kernel, kLds); st != DUO_OK) return st;
-  hipLaunchKernelGGL(split_gemm_kernel, dim3((unsigned)(rup(groups, 8) * 32), (unsigned)(d.dual ? 2 : nb)), dim3(512),
-                     kLds, s, A);
+  hipLaunchKernelGGL(split_gemm_kernel, dim3((unsigned)(rup(groups, 8) * 32), (unsigned)np), dim3(512), kLds, s, A);
   DUO_LAUNCH_CHECK();
   return DUO_OK;
 }

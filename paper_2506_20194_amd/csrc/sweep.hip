@@ -24,6 +24,7 @@
 //            fp32 MFMA GEMM (W0 = the columns' values before pruning).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "internal.h"
@@ -947,10 +948,39 @@ SweepWs carve(void* ws, int64_t n, int64_t k, int B) {
   return w;
 }
 
+// The Y form's lazy products of columns [c0, c1) from the processed columns [u0, u0 +
+// K): W[:, c0:c1] += Z L[c0:c1, u0:u0 + K]^T and Y[:, c0:c1] += V U[u0:u0 + K, c0:c1],
+// independent, one launch.  EW: at u0's column of the pairs (row stride 2 S)
+GemmDesc y_products(int64_t n, int64_t k, int64_t c0, int64_t c1, int64_t u0, int K, int64_t S, const float* EW,
+                    const float* L, int64_t ldl, const float* U, int64_t ldu, float* W, float* Y) {
+  GemmDesc g{};
+  g.M = (int)n;
+  g.N = (int)(c1 - c0);
+  g.C = W + c0;
+  g.C2 = Y + c0;
+  g.ldc = k;
+  g.beta = 1.f;
+  g.tri = TRI_ALL;
+  g.nterms = 2;
+  g.dual = 1;
+  g.t[0] = GemmTerm{EW, 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, 1.f, KLO_ZERO, KHI_FULL};
+  g.t[1] = GemmTerm{EW + S, 2 * S, 1, U + u0 * ldu + c0, ldu, 1, K, 1.f, KLO_ZERO, KHI_FULL};
+  return g;
+}
+
 }  // namespace
 
 size_t sweep_ws_bytes(int64_t n, int64_t k, int B) { return carve(nullptr, n, k, B).bytes; }
-size_t sweep_pk_bytes(int64_t n, int64_t k, int B) { return split_bytes(n, k, super_width(B), 2); }
+
+size_t sweep_pk_bytes(int64_t n, int64_t k, int B) {
+  // of the products of whole super-blocks (those of one block are too short to pay)
+  const int64_t S = super_width(B);
+  size_t most = 0;
+  for (int64_t c0 = S; c0 < k; c0 += S)
+    most = std::max(most, split_bytes(y_products(n, k, c0, k, c0 - S, (int)S, S, nullptr, nullptr, k, nullptr, k, nullptr,
+                                                 nullptr)));
+  return most;
+}
 
 duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64_t ldw, const float* L, int64_t ldl,
                      const float* D, int64_t ldd, const float* fac, double p_w, const SweepOpts& o, int B,
@@ -1077,33 +1107,25 @@ duo_status sweep_run(const void* W, int32_t w_dtype, int64_t n, int64_t k, int64
     const int64_t u0 = j1 < sb1 ? j0 : sb0, c0 = j1, c1 = j1 < sb1 ? sb1 : k;
     if (c0 < c1) {
       const int K = (int)(j1 - u0);
-      GemmDesc g{};
-      g.M = (int)n;
-      g.N = (int)(c1 - c0);
-      g.C = W_out + c0;
-      g.ldc = k;
-      g.beta = 1.f;
-      g.tri = TRI_ALL;
-      g.nterms = 2;
+      prof_begin(DUO_PROF_TRAIL, s);
+      duo_status st;
       if (yr) {
-        // W[:, c0:c1] += Z L[c0:c1, u0:j1]^T and Y[:, c0:c1] += V U[u0:j1, c0:c1]:
-        // independent, one launch
-        g.dual = 1;
-        g.C2 = Y + c0;
-        g.t[0] = GemmTerm{w.EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, 1.f, KLO_ZERO, KHI_FULL};
-        g.t[1] = GemmTerm{w.EW + S + (u0 - sb0), 2 * S, 1, U + u0 * ldu + c0, ldu, 1, K, 1.f, KLO_ZERO, KHI_FULL};
-        prof_begin(DUO_PROF_TRAIL, s);
-        duo_status st = gemm_f32_split(g, pk, pk_bytes, s);
-        prof_end(DUO_PROF_TRAIL, s);
-        if (st != DUO_OK) return st;
+        st = gemm_f32_split(y_products(n, k, c0, c1, u0, K, S, w.EW + (u0 - sb0), L, ldl, U, ldu, W_out, Y), pk, pk_bytes, s);
       } else {
+        GemmDesc g{};
+        g.M = (int)n;
+        g.N = (int)(c1 - c0);
+        g.C = W_out + c0;
+        g.ldc = k;
+        g.beta = 1.f;
+        g.tri = TRI_ALL;
+        g.nterms = 2;
         g.t[0] = GemmTerm{w.EW + (u0 - sb0), 2 * S, 1, L + c0 * ldl + u0, ldl, 0, K, -1.f, KLO_ZERO, KHI_FULL};
         g.t[1] = GemmTerm{w.EW + S + (u0 - sb0), 2 * S, 1, D + u0 * ldd + c0, ldd, 1, K, 1.f, KLO_ZERO, KHI_FULL};
-        prof_begin(DUO_PROF_TRAIL, s);
-        duo_status st = gemm_f32(g, s);
-        prof_end(DUO_PROF_TRAIL, s);
-        if (st != DUO_OK) return st;
+        st = gemm_f32(g, s);
       }
+      prof_end(DUO_PROF_TRAIL, s);
+      if (st != DUO_OK) return st;
     }
   }
   if (mask_out || W_out_lowp) {

@@ -53,6 +53,18 @@ def test_workspace_sizes(duo_lib):
     assert ws(99, 1, 1, 1, 1) == 0
 
 
+@pytest.mark.parametrize("n,k,packed", [(256, 512, False), (4096, 4096, False), (28672, 4096, False), (64, 6144, False),
+                                        (64, 8192, True), (4096, 8192, True), (8192, 28672, True)])
+def test_prune_workspace_holds_what_is_used(duo_lib, n, k, packed):
+    """duo_prune_layer's workspace is the sum of its parts, and packed operands are
+    added only for sizes whose products use them."""
+    ws = duo_lib.duo_workspace_size
+    parts = sum((b + 255) // 256 * 256 for b in (
+        4 * max(n, k) * k, 4 * k, ws(duo_lib.DUO_OP_SCORE_TERMS, 0, k, 0, 0), ws(duo_lib.DUO_OP_SWEEP, n, k, 0, 128)))
+    got = ws(duo_lib.DUO_OP_PRUNE_LAYER, n, k, 0, 128)
+    assert (got > parts) == packed and (packed or got == parts), (got, parts)
+
+
 def _rule(p=0.5, kind=1):
     from paper_2506_20194_amd.duo import ActRule
 
