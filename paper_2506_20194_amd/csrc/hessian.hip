@@ -10,10 +10,10 @@
 //               for two input streams, the low part of dX) in an MFMA-ready
 //               token-blocked layout [token block][group][channel][16 bytes];
 //               also sums dX^2 per channel;
-//   gram        gram_bf16_kernel (256 x 128 tiles) or gram_f32_kernel over the
-//               tiles at and below the diagonal: one pass over the tokens
-//               yields H_ij, G_ij and G_ji;
-//   reductions  fixed-order sums of the partial tiles (deterministic).
+//   gram        gram_bf16_kernel or gram_f32_kernel over 256 x 256 tiles, each of H
+//               (on and above the diagonal) or of G (there, or everywhere);
+//   reductions  fixed-order sums of the partial tiles (deterministic), and H's
+//               lower triangle from its upper one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -834,6 +834,7 @@ struct GramArgs {
   int nsplit, nseg;  // the last nsplit tiles of the order are split into nseg token segments
   int seg_len, ntb;  // token blocks per segment, in all
   int piece;         // token blocks that one set of accumulators sums up
+  float* run;        // [whole tiles][256 * 256]: sums of their pieces so far, or NULL
   float* H;
   int64_t ldh;
   float* G;
@@ -914,8 +915,8 @@ __device__ inline int gram_order(const GramArgs<T>& A, int o) {
   return !A.mixed ? o : (o < ng ? A.nh + o : o - ng);
 }
 
-// Work of a workgroup: a whole tile (*part < 0), or token segment *seg of a split
-// tile whose partial is number *part.  Each XCD takes a contiguous range of the
+// Work of a workgroup: a whole tile (*part = -1 - its number), or token segment *seg
+// of a split tile whose partial is number *part.  Each XCD takes a contiguous range of the
 // whole tiles (of the whole G tiles and of the whole H tiles when mixed: an XCD
 // that held only the dearer kind would finish last; neighbouring tiles share
 // operand panels in that XCD's L2), then one of the segments, segment by segment.
@@ -927,13 +928,14 @@ __device__ inline bool gram_unit(const GramArgs<T>& A, int* tile, int* seg, int*
   const int n1 = A.mixed ? min(A.ntiles - A.nh, nfull) : nfull, n2 = nfull - n1, n3 = A.nsplit * A.nseg;
   const int p1 = (n1 + 7) / 8, p2 = (n2 + 7) / 8, p3 = (n3 + 7) / 8;
   *seg = 0;
-  *part = -1;
   if (y < p1) {
+    *part = -1 - (x * p1 + y);
     *tile = gram_order(A, x * p1 + y);
     return x * p1 + y < n1;
   }
   y -= p1;
   if (y < p2) {
+    *part = -1 - (n1 + x * p2 + y);
     *tile = gram_order(A, n1 + x * p2 + y);
     return x * p2 + y < n2;
   }
@@ -947,19 +949,40 @@ __device__ inline bool gram_unit(const GramArgs<T>& A, int* tile, int* seg, int*
 }
 
 // End of a piece in both Gram kernels: the tile's accumulators to the partial
-// tile of its segment (stored first, then added to), or added to H or G.  The
+// tile of its segment (stored first, then added to), or added to H or G; of a whole
+// tile with several pieces (`run`) to its running sum, which joins H or G with the
+// last piece, so that H and G are rounded once per call.  The running sum is kept
+// as the lanes hold it, 1 KB per access.  The
 // products run with the tile's columns (J) as the MFMA's rows, so that a lane
 // holds four consecutive entries of one row: accumulator element r of block (a,
 // b) is row 64 wj + 16 b + lane % 16, column 128 wi + 16 a + 4 (lane / 16) + r.
 // Sixteen 16-byte reads per lane are in flight at a time, with no LDS and no
 // barrier (staged through LDS, a piece cost 44 us at k = 4096; here 25).
 template <typename T>
-__device__ inline void gram_store(const GramArgs<T>& A, int isg, int I, int J, int part, bool first,
-                                  const f4 (&acc)[8][4]) {
+__device__ inline void gram_store(const GramArgs<T>& A, int isg, int I, int J, int part, bool first, bool last,
+                                  f4 (&acc)[8][4]) {
   // opaque, so that the addresses of a piece's stores are not kept in registers
   // through the main loop
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
+  if (part < 0 && A.run && !(first && last)) {  // uniform
+    f4* const r = (f4*)(A.run + (int64_t)(-1 - part) * GT * GT) + tid;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (!first) {
+        f4 c[8];
+#pragma unroll
+        for (int a = 0; a < 8; ++a) c[a] = r[(8 * b + a) * 512];
+#pragma unroll
+        for (int a = 0; a < 8; ++a) acc[a][b] = c[a] + acc[a][b];
+      }
+      if (!last)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) r[(8 * b + a) * 512] = acc[a][b];
+      __builtin_amdgcn_sched_barrier(0);  // 8 reads at a time, for the registers
+    }
+    if (!last) return;
+  }
   const int lane = tid & 63, wave = tid >> 6;
   const int r0 = (wave & 3) * 64 + (lane & 15), c0 = (wave >> 2) * 128 + 4 * (lane >> 4);
   float* base;  // of the tile
@@ -1088,7 +1111,7 @@ __global__ __launch_bounds__(512) void gram_f32_kernel(GramArgs<float> A) {
     for (int a = 0; a < 8; ++a)
 #pragma unroll
       for (int b = 0; b < 4; ++b) asm volatile("s_nop 1" : "+v"(acc[a][b]));  // the last products have been written
-    gram_store(A, isg, I, J, part, p0 == tb0, acc);
+    gram_store(A, isg, I, J, part, p0 == tb0, p1 >= tb1, acc);
     pp::lds_barrier();  // every wave is done with the stages
     p0 = p1;
   } while (p0 < tb1);
@@ -1167,7 +1190,7 @@ __global__ __launch_bounds__(512) void gram_bf16_kernel(GramArgs<uint16_t> A) {
       };
       pp::pp_loop<4, 2, 2>(nst, acc, issue, read_a, read_b);
     }
-    gram_store(A, isg, I, J, part, p0 == tb0, acc);
+    gram_store(A, isg, I, J, part, p0 == tb0, p1 >= tb1, acc);
     pp::lds_barrier();  // every wave is done with the units
     p0 = p1;
   } while (p0 < tb1);
@@ -1278,62 +1301,12 @@ int64_t hessian_chunk_tokens(int64_t m, int64_t k) {
   return m < ch ? (m < 1 ? 1 : m) : ch;
 }
 
-// Which tiles are split into token segments.  Whole rounds of 256 tiles (one per
-// CU) run unsplit; the rest of the tiles, or all of them when there is less than
-// one round, are split so that their segments fill the chip once more, at the
-// price of summing the partial tiles afterwards.  Model, per tile of `ch` tokens:
-// 2 * 256^2 * ch flop at 5.5 TFLOP/s (bf16) or 0.5 (fp32) per CU, 8 us of start
-// and epilogue per round; the sum of s partials reads s tiles and reads and
-// writes the output, (s + 2) * 256 KB at about 4 TB/s, and costs a launch (5 us).
-// `cost2`: two bf16 streams, where a G tile costs twice an H tile; the launch then
-// ends with the H tiles, and the split ones are the last of them.  At k = 4096, 65536
-// tokens (272 tiles) 16 tiles in 16 segments each: 1.06 rounds, where splitting
-// all tiles in 8 took 1.125 rounds and 310 us of sums per call.
-struct GramPlan {
-  int nsplit, nseg;
-};
-// Below one round (k <= 3840) the segments depend on k and the tokens alone (taken for
-// H and G's upper triangle), so that G has the same bits with and without H and
-// in either form.
-static GramPlan gram_plan(int64_t T, int64_t nh, int64_t ng, bool cost2, bool bf16, int64_t ch) {
-  const int64_t ntiles = nh + ng, work = ntiles + (cost2 ? ng : 0), both = T * (T + 1);
-  const bool small = both < 256;
-  const int64_t rest = small ? both : std::min(work % 256, ntiles);  // tiles to split
-  if (rest == 0) return {0, 1};
-  const double t_tile = 2.0 * GT * GT * (double)ch / (bf16 ? 5.5e12 : 0.5e12) * (small && cost2 ? 1.5 : 1.0);
-  const double t_sum = (double)GT * GT * 4.0 / 4e12;
-  int best = 1;
-  double best_cost = 1e30;
-  for (int s = 1; s <= 32; ++s) {
-    if (s > 1 && rest * s > 1024) break;
-    const double rounds = (double)cdiv(rest * s, 256);
-    const double cost = rounds / s * t_tile + rounds * 8e-6 + (s > 1 ? 5e-6 + (double)rest * (s + 2) * t_sum : 0.0);
-    if (cost < best_cost * (1.0 - 1e-9)) {
-      best_cost = cost;
-      best = s;
-    }
-  }
-  return best > 1 ? GramPlan{(int)(small ? ntiles : rest), best} : GramPlan{0, 1};
-}
-
-// Tokens that one set of accumulators sums up: the products of a longer run are
-// added to H, G or the partial tile in pieces.  The relative error of the 32-bit
-// sums grows with the square root of the accumulation steps (32 tokens each in
-// bf16, 4 in fp32): measured 1.5e-6 in one piece of 65536 tokens (bf16, k = 4096),
-// 6.6e-7 in pieces of 16384, 4.6e-7 in pieces of 8192.  A piece costs a pass
-// over the output, whose rows lie further apart the larger k is, and takes the
-// workgroups of an XCD out of step: 25 us at k = 4096 (390 us of products per 16384
-// tokens), 140 us at k = 28672 (131072 tokens: 137 ms in one piece, 152 in pieces of
-// 16384, 167 of 8192).
-// The bound on a piece, of `ch` tokens in a launch: the share of a tile that up to eight
-// segments per tile would get which fill the chip's rounds of 256 tiles (a full tile
-// at 4.5 TFLOP/s per CU, the sum of s partial tiles (s + 2) * 256 KB at 4 TB/s).  That
-// is the longest run that the sums of a launch split throughout would have, and
-// the error stays below theirs: 65536 tokens at k = 4096 8192, 8192 tokens there 2048.
-static int gram_piece(int64_t T, bool bf16, int64_t ch) {
-  const int64_t k = T * GT, ntiles = T * (T + 1), nb = cdiv(ch, kTokBlk);
+// Token segments (up to eight) that fill the chip's rounds of 256 tiles when every
+// tile of a launch is split: a full tile at 4.5 TFLOP/s per CU, the sum of s partial
+// tiles (s + 2) * 256 KB at 4 TB/s.
+static int even_segments(int64_t ntiles, int64_t ch) {
   const double t_tile = 2.0 * GT * GT * (double)ch / 4.5e12, t_sum = (double)GT * GT * 4.0 / 4e12;
-  int64_t best = 1;
+  int best = 1;
   double best_cost = 1e30;
   for (int s = 1; s <= 8; ++s) {
     const double cost = (double)cdiv(ntiles * s, 256) / s * t_tile + (s > 1 ? (double)ntiles * (s + 2) * t_sum : 0.0);
@@ -1342,9 +1315,73 @@ static int gram_piece(int64_t T, bool bf16, int64_t ch) {
       best = s;
     }
   }
+  return best;
+}
+
+// How a launch of nh H tiles and ng G tiles, `ch` tokens each, is divided.
+// Split tiles.  Whole rounds of 256 tiles (one per CU) run unsplit; the rest of the
+// tiles, or all of them when there is less than one round, are split so that their
+// segments fill the chip once more, at the price of summing the partial tiles
+// afterwards.  Model, per tile: 2 * 256^2 * ch flop at 5.5 TFLOP/s (bf16) or 0.5
+// (fp32) per CU, 8 us of start and epilogue per round; the sum of s partials reads s
+// tiles and reads and writes the output, (s + 2) * 256 KB at about 4 TB/s, and costs a
+// launch (5 us).  `cost2`: two bf16 streams, where a G tile costs twice an H tile; the
+// launch then ends with the H tiles, and the split ones are the last of them.  At k =
+// 4096, 65536 tokens (272 tiles) 16 tiles in 16 segments each: 1.06 rounds, where
+// splitting all tiles in 8 took 1.125 rounds and 310 us of sums per call.
+// Up to k = 1024 every form of a launch (H, G, both, all of G) fits one round, and the
+// segments are those of the largest, so that G has the same bits in all of them.
+// Pieces.  One set of accumulators sums up at most `piece` token blocks; the sums of a
+// longer run are added up tile by tile in pieces.  The relative error of the
+// 32-bit sums grows with the square root of the accumulation steps (32 tokens each in
+// bf16, 4 in fp32).  A piece is no longer than the segments of a launch split evenly
+// throughout (even_segments), which decides up to k = 9216 (65536 tokens at k = 9216: 9.0e-7 of
+// H).  Above, where that is one segment, 24576 tokens up to k = 20480 and no bound
+// beyond: a piece costs a pass over the output, whose rows lie further apart the
+// larger k is, and takes the workgroups of an XCD out of step (65536 tokens, in one
+// piece, pieces of 24576 and of 16384: k = 11008 12.20, 12.33, 12.45 ms with errors of 1.4e-6,
+// 1.1e-6, 8.8e-7; k = 20480 39.1, 40.2, 40.8 ms; k = 24576 55.3, 57.0, 58.1 ms).
+struct GramPlan {
+  int nsplit, nseg;  // the last nsplit tiles in nseg segments each
+  int piece;         // token blocks
+  bool run;          // whole tiles keep running sums
+};
+static GramPlan gram_plan(int64_t T, int64_t nh, int64_t ng, bool cost2, bool bf16, int64_t ch) {
+  const int64_t ntiles = nh + ng, nb = rup(cdiv(ch, kTokBlk), 2), k = T * GT;
+  const bool small = T <= 4;
+  int64_t rest;     // tiles to split
+  double each = 1;  // what one of them costs, in H tiles
+  if (small) {
+    rest = T * T + T * (T + 1) / 2;
+    if (cost2) each = 2;
+  } else {
+    rest = cost2 && nh > 0 ? std::min((ntiles + ng) % 256, ntiles) : ntiles % 256;
+    if (cost2 && rest > nh) each = (double)(rest + rest - nh) / (double)rest;
+  }
+  int best = 1;
+  if (rest > 0) {
+    const double t_tile = 2.0 * GT * GT * (double)ch / (bf16 ? 5.5e12 : 0.5e12) * each;
+    const double t_sum = (double)GT * GT * 4.0 / 4e12;
+    double best_cost = 1e30;
+    for (int s = 1; s <= 32; ++s) {
+      if (s > 1 && rest * s > 1024) break;
+      const double rounds = (double)cdiv(rest * s, 256);
+      const double cost = rounds / s * t_tile + rounds * 8e-6 + (s > 1 ? 5e-6 + (double)rest * (s + 2) * t_sum : 0.0);
+      if (cost < best_cost * (1.0 - 1e-9)) {
+        best_cost = cost;
+        best = s;
+      }
+    }
+  }
+  GramPlan p;
+  p.nsplit = best > 1 ? (int)(small ? ntiles : rest) : 0;
+  p.nseg = best;
+  const int even = even_segments(small ? T * (T + 1) / 2 : ntiles, ch);
   const int64_t t = k <= 9216 ? 16384 : k <= 20480 ? 24576 : 131072;
   const int64_t most = (bf16 ? t : k <= 9216 ? 4096 : 8192) / kTokBlk;
-  return (int)std::min(most, rup(cdiv(nb, best), 2));
+  p.piece = (int)std::min(most, rup(cdiv(nb, even), 2));
+  p.run = even > 1 && p.piece < nb && p.nsplit < ntiles;
+  return p;
 }
 
 // Diagonal of H in fp64 for act_order: hdiag[c] += sum_t Xh[t][c]^2, read
@@ -1395,6 +1432,7 @@ struct HessWs {
   uint8_t* Pl;
   float* apart;
   float* part;
+  float* run;
   double* dpart;
   size_t bytes;
 };
@@ -1411,8 +1449,11 @@ static int diag_slices(int64_t kp, int ntb) {
 
 // Token blocks per packing workgroup: eight, or fewer where that leaves CUs idle
 // (2048 x 512 fp32 in 16 workgroups of eight 56 us; with one block each the whole layer is 60 us
-// shorter).
-static int pack_blocks(int64_t mc, int64_t kp) {
+// shorter).  fp32: no more than a workgroup per CU, whose 256 rows of 128 bytes
+// per operand the vector cache barely holds (8192 x 2048, two streams: two blocks each
+// 1577 us, eight 1467, four 1359).
+static int pack_blocks(int64_t mc, int64_t kp, bool f32) {
+  if (f32) return (int)std::min<int64_t>(8, cdiv(kp / 256 * cdiv(mc, kTokBlk), 256));
   const int64_t wg = kp / 256 * cdiv(mc, 256);
   return wg >= 512 ? 8 : wg >= 128 ? 2 : 1;
 }
@@ -1425,13 +1466,14 @@ static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   const int64_t kp = rup(k, GT);
   const int64_t tokp = rup(ch, 256);
   const int64_t T = kp / GT;
-  // partial tiles: enough for every form (with and without H; all of G, its upper
-  // triangle or none; one stream or two; either dtype)
-  int64_t part_tiles = 0;
+  // partial tiles and running sums: enough for every form (with and without H; all
+  // of G, its upper triangle or none; one stream or two; either dtype)
+  int64_t part_tiles = 0, run_tiles = 0;
   for (int f = 0; f < 24; ++f) {
     const int64_t up = T * (T + 1) / 2, nh = f & 1 ? up : 0, ng = f / 8 == 0 ? 0 : f / 8 == 1 ? up : T * T;
     const GramPlan p = gram_plan(T, nh, ng, f & 2, f & 4, ch);
-    part_tiles = std::max(part_tiles, (int64_t)p.nsplit * (p.nseg > 1 ? p.nseg : 0));
+    part_tiles = std::max(part_tiles, (int64_t)p.nsplit * p.nseg);
+    if (p.run) run_tiles = std::max(run_tiles, nh + ng - p.nsplit);
   }
   Carver c(ws);
   HessWs h;
@@ -1442,6 +1484,7 @@ static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   h.Pl = c.take<uint8_t>((size_t)tokp * kp * 2);  // low part exists for bf16 only
   h.apart = c.take<float>((size_t)std::max((tokp / 256) * kp, kApartMin));
   h.part = c.take<float>(part_tiles > 0 ? (size_t)part_tiles * GT * GT : 1);
+  h.run = c.take<float>((size_t)run_tiles * GT * GT);
   h.dpart = c.take<double>((size_t)diag_slices(kp, kDiagSlices) * kp);
   h.bytes = c.off;
   return h;
@@ -1500,7 +1543,7 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
       st = launch_act_select<T>(xd, ldx, mc, (int)k, 0, w.thr + rup(ch, 256), w.flags, s);
       if (st != DUO_OK) return st;
     }
-    const int tpb = pack_blocks(mc, kp), prow = (int)cdiv(rup(mc, 2 * kTokBlk) / kTokBlk, tpb);
+    const int tpb = pack_blocks(mc, kp, sizeof(T) == 4), prow = (int)cdiv(rup(mc, 2 * kTokBlk) / kTokBlk, tpb);
     dim3 pg((unsigned)(kp / 256), (unsigned)prow);
     if constexpr (sizeof(T) == 2) {
       if (bf16_vec_ok(xs, ldx, k) && (!two || bf16_vec_ok(xd, ldx, k))) {
@@ -1550,7 +1593,8 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
     A.nh = want_h ? nh_all : 0;
     A.ntiles = A.nh + ng;
     A.g_full = g_full;
-    A.piece = gram_piece(nt, sizeof(T) == 2, ch);
+    A.piece = plan.piece;
+    A.run = plan.run ? w.run : nullptr;
     A.mixed = lo;
     A.nsplit = plan.nsplit;
     A.nseg = plan.nseg;
