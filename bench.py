@@ -22,10 +22,9 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_FP32_TFLOPS = 157.3    # MI355X dense fp32 MFMA
-# Large fp32 products run as six bf16 products of exactly split operands: from this
-# k up most of the score and lazy-update flop do (not the factorisation's, nor a
-# quantised layer's), and their rates are priced against a sixth of the bf16 peak
-SPLIT_MIN_K = 7168
+# Large fp32 products of the sweep's Y form run as six bf16 products of exactly split
+# operands where the library's dispatch finds that faster (not the factorisation's, nor a
+# quantised layer's); their rates are priced against a sixth of the bf16 peak
 PEAK_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 
@@ -36,10 +35,10 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # were taken on: any change to that file makes the figure unknown (null).
 GRAM_TRAFFIC = {
     "source": "paper_2506_20194_amd/csrc/hessian.hip",
-    "sha256": "f3de6573c603ce6742dc580baace072e5fed57319ec9cf1f59ad4340a65b7e22",
+    "sha256": "a7859ef85061e7302eb00ca2333acdc8be1c250ef49274033772ca18efefb441",
     "workload": "llama2_70b_down_proj",
-    "fetch_kib": 171116373.3, "fetch_scale": 2.0,
-    "write_kib": 3239936.0, "write_scale": 1.0,
+    "fetch_kib": 169630073.3, "fetch_scale": 2.0,
+    "write_kib": 3505632.8, "write_scale": 1.0,
 }
 
 
@@ -48,11 +47,19 @@ GRAM_TRAFFIC = {
 # counters and calibration as above.
 DECODE_TRAFFIC = {
     "source": "paper_2506_20194_amd/csrc/decode.hip",
-    "sha256": "52129b94b57f5945de044bea60793798ef5b96b211fd4819029d5ca90d8fdf73",
+    "sha256": "23dcd580fb35eeb921eee599a5fb3cca4c74a19a44be110ecb7bfce42f29acc9",
     "workload": "llama2_70b_down_proj",
-    "fetch_kib": 55169.4, "fetch_scale": 2.0,
+    "fetch_kib": 55165.1, "fetch_scale": 2.0,
     "write_kib": 2048.0, "write_scale": 1.0,
 }
+
+
+def packed_bytes(duo, n, k, block=128):
+    """Packed operands in duo_prune_layer's workspace (0: no product of this size is
+    split; 12 k^2 and more: the score product is): its size less its other parts."""
+    ws = duo.duo_workspace_size
+    parts = (4 * max(n, k) * k, 4 * k, ws(duo.DUO_OP_SCORE_TERMS, 0, k, 0, 0), ws(duo.DUO_OP_SWEEP, n, k, 0, block))
+    return ws(duo.DUO_OP_PRUNE_LAYER, n, k, 0, block) - sum((b + 255) // 256 * 256 for b in parts)
 
 
 def gram_traffic(workload, t=None):
@@ -493,9 +500,11 @@ def main():
     # inverse, Cholesky, full products) and is printed beside it
     chol_score_flop = (3 if yform else 4) * k ** 3 / 3
     chol_score_flop_plain = 8 * k ** 3 / 3
-    f32_peak = PEAK_SPLIT_TFLOPS if k >= SPLIT_MIN_K and not args.quant else PEAK_FP32_TFLOPS
+    split = packed_bytes(duo, n, k) if yform and not args.quant else 0
+    f32_peak = PEAK_SPLIT_TFLOPS if split else PEAK_FP32_TFLOPS
+    score_peak = PEAK_SPLIT_TFLOPS if split >= 12 * k * k else PEAK_FP32_TFLOPS
     # the factorisation's two thirds of k^3 at the fp32 peak, the score terms' rest at theirs
-    chol_score_peak = chol_score_flop / (2 * k ** 3 / 3 / PEAK_FP32_TFLOPS + (chol_score_flop - 2 * k ** 3 / 3) / f32_peak)
+    chol_score_peak = chol_score_flop / (2 * k ** 3 / 3 / PEAK_FP32_TFLOPS + (chol_score_flop - 2 * k ** 3 / 3) / score_peak)
     # the Gram kernel multiplies in the calibration input's precision: bf16
     # MFMA for bf16 inputs, fp32 MFMA for fp32 inputs
     gram_peak = PEAK_BF16_TFLOPS if c["x_dtype"] == torch.bfloat16 else PEAK_FP32_TFLOPS

@@ -957,7 +957,7 @@ __device__ inline bool gram_unit(const GramArgs<T>& A, int* tile, int* seg, int*
 // holds four consecutive entries of one row: accumulator element r of block (a,
 // b) is row 64 wj + 16 b + lane % 16, column 128 wi + 16 a + 4 (lane / 16) + r.
 // Sixteen 16-byte reads per lane are in flight at a time, with no LDS and no
-// barrier (staged through LDS, a piece cost 44 us at k = 4096; here 25).
+// barrier (adding a piece to H or G at k = 4096: 44 us staged through LDS, 25 so).
 template <typename T>
 __device__ inline void gram_store(const GramArgs<T>& A, int isg, int I, int J, int part, bool first, bool last,
                                   f4 (&acc)[8][4]) {
@@ -1123,10 +1123,10 @@ __global__ __launch_bounds__(512) void gram_f32_kernel(GramArgs<float> A) {
 // [128 channels][16 bytes], filled from the packed operands in 1 KB pieces, and a
 // fragment read is linear in it (no bank conflicts).  Two streams: dX = hi + lo,
 // and a G tile takes both in turn for every 64 tokens (twice an H tile's stages).
-// Bound: MFMA issue and the clock under that load.  Measured, whole calls:
-// 2 x 65536 tokens at k = 4096 5.17 -> 4.27 ms; one chunk: 8192 tokens, two streams, k = 11008 3360 -> 2150
-// us; 131072 at k = 28672 166 -> 137 ms (the form before had all eight waves in step on a ring of 32-token stages,
-// and gave four XCDs the H tiles and four the G tiles).
+// Bound: MFMA issue and the clock under that load.  Measured, whole calls: 2 x 65536
+// tokens at k = 4096 5.16 -> 4.16 ms; 2 x 8192, two streams, k = 11008 7.42 -> 5.18 ms;
+// one launch of 131072 at k = 28672 166 -> 140 ms (the form before had all eight waves in
+// step on a ring of 32-token stages, and gave four XCDs the H tiles and four the G tiles).
 constexpr int kGram16Unit = 128 * 128;  // bytes: 128 channels x 64 tokens
 constexpr size_t kGram16Lds = (size_t)8 * kGram16Unit;
 __global__ __launch_bounds__(512) void gram_bf16_kernel(GramArgs<uint16_t> A) {

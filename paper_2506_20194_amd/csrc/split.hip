@@ -2,9 +2,9 @@
 // three bf16 parts, x = h + m + l (8 significant bits each, round to nearest), and
 //   a b = l_a h_b + h_a l_b + m_a m_b + m_a h_b + h_a m_b + h_a h_b
 // is accumulated in fp32, smallest terms first; of the three terms left out m_a l_b and
-// l_a m_b reach 2^-25 |a b| each (measured below).  A term is exact, and per 64 k the accumulators are rounded
-// 12 times where v_mfma_f32_16x16x4_f32 rounds them 16 times.  Six bf16 products at
-// about 1500 TFLOP/s are an fp32 product at 250, against 125-137 on the fp32 matrix
+// l_a m_b reach 2^-25 |a b| each.  A term is exact, and per 64 k the accumulators are
+// rounded 12 times where v_mfma_f32_16x16x4_f32 rounds them 16 times.  Six bf16 products
+// at about 1500 TFLOP/s are an fp32 product at 250, against 125-137 on the fp32 matrix
 // instructions (157 peak).
 //
 // The operands are packed first (pack_kernel; 6 bytes per element) into the layout
@@ -158,10 +158,11 @@ __device__ inline bool split_tile(const SplitArgs& A, int* ti, int* tj) {
 // 256 x 256 tile per 512-thread workgroup, the part of a wave 128 columns x 64
 // rows (the tile's columns as the MFMA's rows, so that a lane holds four
 // consecutive entries of a row of C).  Bound: MFMA issue and the clock under that
-// load, and C (read and written by all CUs at about the same time): 8192 x 27648, K =
-// 1024, two products in one launch, 4.3 ms, 216 TFLOP/s of fp32 flop, where the fp32
-// matrix instructions took 7.4 ms. Error against 64 bits (L of k = 11008): 3.8e-6
-// before, 2.8e-6 now.
+// load, and C (read and written by all CUs at about the same time): 8192 x 10240, K =
+// 1024, two products with their packing 1.57 ms, 218 TFLOP/s of fp32 flop, where the
+// fp32 matrix instructions take 2.63 ms.  Error against 64 bits of the weights of a
+// whole solve, from the same 32-bit L, G and a (fp32 instructions, here): k = 8192 1.29e-6,
+// 1.10e-6; k = 11008 1.76e-6, 1.48e-6; k = 14336 2.31e-6, 1.93e-6.
 __global__ __launch_bounds__(512) void split_gemm_kernel(SplitArgs A) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];  // [stage parity][columns 0, 1, rows 0, 1]
   int ti, tj;
