@@ -1431,8 +1431,7 @@ struct HessWs {
   uint8_t* Pz;
   uint8_t* Pl;
   float* apart;
-  float* part;
-  float* run;
+  float* part;  // partial tiles, then the running sums of whole tiles
   double* dpart;
   size_t bytes;
 };
@@ -1467,13 +1466,13 @@ static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   const int64_t tokp = rup(ch, 256);
   const int64_t T = kp / GT;
   // partial tiles and running sums: enough for every form (with and without H; all
-  // of G, its upper triangle or none; one stream or two; either dtype)
-  int64_t part_tiles = 0, run_tiles = 0;
+  // of G, its upper triangle or none; one stream or two; either dtype).  Each form needs
+  // no less for more tokens, so a workspace for m tokens serves any smaller m
+  int64_t part_tiles = 0;
   for (int f = 0; f < 24; ++f) {
     const int64_t up = T * (T + 1) / 2, nh = f & 1 ? up : 0, ng = f / 8 == 0 ? 0 : f / 8 == 1 ? up : T * T;
     const GramPlan p = gram_plan(T, nh, ng, f & 2, f & 4, ch);
-    part_tiles = std::max(part_tiles, (int64_t)p.nsplit * p.nseg);
-    if (p.run) run_tiles = std::max(run_tiles, nh + ng - p.nsplit);
+    part_tiles = std::max(part_tiles, (int64_t)p.nsplit * p.nseg + (p.run ? nh + ng - p.nsplit : 0));
   }
   Carver c(ws);
   HessWs h;
@@ -1484,7 +1483,6 @@ static HessWs carve_hessian(void* ws, int64_t m, int64_t k) {
   h.Pl = c.take<uint8_t>((size_t)tokp * kp * 2);  // low part exists for bf16 only
   h.apart = c.take<float>((size_t)std::max((tokp / 256) * kp, kApartMin));
   h.part = c.take<float>(part_tiles > 0 ? (size_t)part_tiles * GT * GT : 1);
-  h.run = c.take<float>((size_t)run_tiles * GT * GT);
   h.dpart = c.take<double>((size_t)diag_slices(kp, kDiagSlices) * kp);
   h.bytes = c.off;
   return h;
@@ -1594,7 +1592,7 @@ static duo_status hessian_typed(const T* Xs, const T* Xd, int64_t m, int64_t k, 
     A.ntiles = A.nh + ng;
     A.g_full = g_full;
     A.piece = plan.piece;
-    A.run = plan.run ? w.run : nullptr;
+    A.run = plan.run ? w.part + (int64_t)plan.nsplit * plan.nseg * GT * GT : nullptr;
     A.mixed = lo;
     A.nsplit = plan.nsplit;
     A.nseg = plan.nseg;

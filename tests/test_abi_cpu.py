@@ -65,6 +65,13 @@ def test_prune_workspace_holds_what_is_used(duo_lib, n, k, packed):
     assert (got > parts) == packed and (packed or got == parts), (got, parts)
 
 
+@pytest.mark.parametrize("k", [64, 256, 300, 512, 1000, 1536, 2816, 3328, 3584, 4096, 8448, 11008, 20480, 28672, 32768])
+def test_hessian_workspace_serves_fewer_tokens(duo_lib, k):
+    sizes = [duo_lib.duo_workspace_size(duo_lib.DUO_OP_HESSIAN, 0, k, m, 0)
+             for m in sorted({int(1.05 ** i) for i in range(245)})]
+    assert sizes == sorted(sizes)
+
+
 def _rule(p=0.5, kind=1):
     from paper_2506_20194_amd.duo import ActRule
 
