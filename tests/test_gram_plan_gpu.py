@@ -142,3 +142,33 @@ def test_run_lengths(duo_lib, k, m):
         ref = Gr if full else torch.where(i[:, None] <= i[None, :], Gr, 0.0)
         run = _even_run(k, m, (t * t if full else half) + (half if with_h else 0))
         assert (G.double() - ref).norm() <= 0.33 * 2.0 ** -24 * (run / 32) ** 0.5 * ref.norm(), (with_h, full)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_second_chunk(duo_lib, dtype):
+    # tokens go through the kernels in chunks of at most 131072
+    _run(duo_lib, 264, 131072 + 333, dtype, False)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("k,m", [(520, 3000), (4096, 8200)])
+def test_nonfinite_entry(duo_lib, k, m, dtype):
+    """One infinite and one NaN entry: H and G are non-finite exactly in the rows and
+    columns that the two tokens' products reach, and the sums elsewhere are kept."""
+    print("[case] gram non-finite", k, m, dtype, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(k)
+    X = torch.randn((m, k), generator=g, device="cuda").to(dtype)
+    X[m // 3, 5], X[m - 1, k - 2] = float("inf"), float("nan")
+    H, G, a = (torch.zeros(s, device="cuda") for s in ((k, k), (k, k), (k,)))
+    duo_lib.duo_hessian_accum(X, H, 0.5, G=G, a=a)
+    z = int(0.5 * k + 0.5)
+    mag = torch.where(X.isnan(), float("inf"), X.abs().float())  # neither is among the smaller half
+    drop = torch.zeros((m, k), dtype=torch.bool, device="cuda").scatter(1, torch.sort(mag, dim=1, stable=True).indices[:, :z], True)
+    Xh, dX = X.masked_fill(drop, 0.0).double(), X.masked_fill(~drop, 0.0).double()
+    i = torch.arange(k, device="cuda") // 256
+    up = i[:, None] <= i[None, :]
+    for got, ref, part in ((H, Xh.t() @ Xh, torch.ones_like(up)), (G, dX.t() @ Xh, up)):
+        assert torch.equal(got.isfinite()[part], ref.isfinite()[part])
+        ok = part & ref.isfinite()
+        assert ((got.double() - ref).abs()[ok] <= 2e-5 * m).all()
+    assert ((a.double() - dX.square().sum(0)).abs() <= 2e-5 * (dX.square().sum(0) + 1.0)).all()
